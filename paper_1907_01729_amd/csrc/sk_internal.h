@@ -96,6 +96,29 @@ hipError_t launch_tiled(const FwdArgs &a, void *ws, hipStream_t st);
 // semantics: the length of the whole line).
 int tiled_describe(const FwdArgs &a, char *buf, size_t len);
 
+// A shared cost that splits over two axes (sk_separable.hip).
+struct SepArgs {
+    // Device state: mode[0] = the block size of the line sums (16 or 4) when
+    // the cost splits, else 0; mode[1], mode[2] = the two grids' widths.
+    int32_t *mode;  // null: the sweeps only
+    float *table;   // line tables
+    const float *mu, *nu, *C;
+    float *a;        // [B, d1] base-2 row potentials at the start in, alpha out
+    float *bbuf;     // [2][B, d2p] scratch: base-2 column potentials
+    float *beta, *loss, *merr;
+    int32_t *iters;
+    int32_t *state;  // [B] iterations run, out
+    int B, d1, d2, d2p, n_iter;
+    float s, tol;
+    size_t lds32, lds64;  // dynamic LDS bytes of the solve, lines of up to 32 or 64 entries (0: no such pair of widths)
+};
+// Whether a batch may take it (then the launch shape is filled in; the
+// pointers and sizes above are the caller's).
+bool separable_plan(int B, int d1, int d2, int n_iter, size_t table_bytes, SepArgs *P);
+// Tests the cost; if it splits, sets mode and solves every problem: all outputs
+// written, state > 0.
+hipError_t launch_separable(const SepArgs &P, hipStream_t st);
+
 hipError_t launch_backward(const BwdArgs &a, hipStream_t st);
 
 // Gradient of the sharp loss E^0 (implicit differentiation of the plan,

@@ -85,6 +85,11 @@ struct TiledArgs {
     float *alpha_out, *beta_out, *loss_out, *merr_out;
     int32_t *iters_out;
     int B, d1, d2, R, RBS, JC, n_iter, c_batched;
+    // A shared cost that may split over two axes (sk_separable.hip): where the
+    // device says whether it does (null: not asked), and, for the host, the
+    // arguments of its kernels.
+    const int32_t *sep_mode;
+    const SepArgs *sep;
     int d2p;  // row stride of bbuf and part: d2 rounded up to the sweep's column width
               // (entries past d2 stay 0), so sweeps load and store whole rows unmasked
     float s, tol;
@@ -93,6 +98,9 @@ struct TiledArgs {
 __device__ __forceinline__ size_t pidx(const TiledArgs &T, int plane, int r, int b, int j) {
     return (((size_t)plane * T.R + r) * T.B + b) * (size_t)T.d2p + j;
 }
+
+// The cost splits over two axes (found out by launch_separable's kernels; block-uniform).
+__device__ __forceinline__ bool splits(const TiledArgs &T) { return T.sep_mode && T.sep_mode[0] != 0; }
 
 // Work-group sum in a fixed order (deterministic); `red` holds NT/64 floats.
 template <int NT>
@@ -177,6 +185,7 @@ __device__ __forceinline__ float cl_at(const TiledArgs &T, const float *Cb, int 
 // no scalar load.
 template <int W>
 __global__ __launch_bounds__(kMergeThreads) void sk_tiled_col_exact(TiledArgs T) {
+    if (splits(T)) return;  // every problem is solved, its results are out
     const int lane = threadIdx.x;
     const int j = blockIdx.x * kMergeThreads + lane;
     const int r = blockIdx.y, b0 = blockIdx.z * W;
@@ -237,6 +246,7 @@ __device__ float col_lse_exact(const TiledArgs &T, int b, int j) {
 // Merge of the row blocks' (max, sumexp) partials of the first v-update
 // (fixed order): beta of iteration 1.
 __global__ __launch_bounds__(kMergeThreads) void sk_tiled_merge_exact(TiledArgs T) {
+    if (splits(T)) return;
     const int j = blockIdx.x * kMergeThreads + threadIdx.x;
     const int b = blockIdx.y;
     if (j >= T.d2) return;
@@ -459,6 +469,7 @@ __global__ __launch_bounds__(kThreads) void sk_tiled_sweep(TiledArgs T, int k) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int d1 = T.d1, d2 = T.d2;
 
+    if (STATS && !BATCHED && splits(T)) return;  // every problem is solved, its results are out
     const int st = T.state[b];
     if (!STATS && st != 0) return;  // stopped by an earlier merge's test
     const int K = STATS ? (st ? st : T.n_iter) : k;
@@ -922,6 +933,7 @@ __global__ __launch_bounds__(64 * W) void sk_tiled_sweep_shared(TiledArgs T, int
     static_assert(RS % RB == 0 && 64 % RS == 0, "chunks must tile 64-row segments");
     extern __shared__ float lds[];  // [2][RS][D2P]
     const int r = blockIdx.x, g = blockIdx.y;
+    if (STATS && splits(T)) return;  // every problem is solved, its results are out (a sweep sees its state)
     // The wavefront index is uniform: read it into a scalar register so that
     // everything derived from it (problem, staging assignments) is scalar.
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1490,6 +1502,7 @@ __global__ __launch_bounds__(64 * StreamShape<NC4>::W) void sk_tiled_sweep_strea
 template <int NT>
 __global__ __launch_bounds__(NT) void sk_tiled_final(TiledArgs T) {
     __shared__ float red[NT / 64];
+    if (splits(T)) return;
     const int b = blockIdx.x;
     const int st = T.state[b];
     const int K = st ? st : T.n_iter;
@@ -1719,6 +1732,10 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
     const dim3 blk(kThreads);
     hipLaunchKernelGGL(sk_tiled_init, dim3(512), blk, 0, st, T);
     if (T.n_iter > 0) {
+        if (T.sep) {
+            const hipError_t e = launch_separable(*T.sep, st);
+            if (e != hipSuccess) return e;
+        }
         launch_col_exact(T, st);
         const dim3 mblk(kMergeThreads);
         hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), mblk, 0, st, T);
@@ -1885,6 +1902,8 @@ TiledArgs tiled_args(const FwdArgs &a, int kind, void *ws, Layout *Lout) {
     T.sync = T.state + a.B;
     T.order = nullptr;
     T.nlive = nullptr;
+    T.sep_mode = nullptr;
+    T.sep = nullptr;
     T.MS = merge_slices(a.d2);
     T.stopacc = T.MS > 1 ? reinterpret_cast<unsigned long long *>(base + L.stopacc) : nullptr;
     // Fixed point of the split merge's stop test: parts clamped to
@@ -1955,6 +1974,34 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
         T.order = reinterpret_cast<int32_t *>(base + L.order);
         T.nlive = T.order + a.B;
     }
+    // A shared cost that may split over two axes: the tables lie in the second
+    // plane of the column partials, which only the exact first v-update of the
+    // sweeps uses, the mode beside the stop counters.
+    SepArgs sep;
+    if (kind == kKindShared && a.n_iter > 0 &&
+        separable_plan(a.B, a.d1, a.d2, a.n_iter, sizeof(float) * (size_t)T.R * T.B * T.d2p, &sep)) {
+        sep.mode = T.sync + 1;
+        sep.table = T.part + (size_t)T.R * T.B * T.d2p;
+        sep.mu = T.mu;
+        sep.nu = T.nu;
+        sep.C = T.C;
+        sep.a = T.a;
+        sep.bbuf = T.bbuf;
+        sep.state = T.state;
+        sep.beta = T.beta_out;
+        sep.loss = T.loss_out;
+        sep.merr = T.merr_out;
+        sep.iters = T.iters_out;
+        sep.B = T.B;
+        sep.d1 = T.d1;
+        sep.d2 = T.d2;
+        sep.d2p = T.d2p;
+        sep.n_iter = T.n_iter;
+        sep.s = T.s;
+        sep.tol = T.tol;
+        T.sep_mode = sep.mode;
+        T.sep = &sep;
+    }
     if (W == 8) return vec4 ? dispatch_shared<8, true>(T, ncw, st) : dispatch_shared<8, false>(T, ncw, st);
     if (W == 4) return vec4 ? dispatch_shared<4, true>(T, ncw, st) : dispatch_shared<4, false>(T, ncw, st);
     if (stream_shape(a.d2, a.c_batched ? kKindBatched : kKindShared) && ((uintptr_t)a.C % 16) == 0) {
@@ -2014,12 +2061,16 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
                  kMergeColsThreads, merge_slices(a.d2), merge_slices(a.d2) == 1 ? "" : "s");
     else
         snprintf(mrg, sizeof mrg, "the merge folded into the next sweep");
+    SepArgs sep;
+    const bool split = kind == kKindShared && a.n_iter > 0 &&
+                       separable_plan(B, a.d1, a.d2, a.n_iter, sizeof(float) * (size_t)R * B * padded_width(a.d2, kind), &sep);
     const bool compact = W && a.tol > 0.f && a.select != SK_SELECT_NO_COMPACTION;
     const int nchunk = (a.B + kTiledMaxBatch - 1) / kTiledMaxBatch;
     char chunks[64] = "";
     if (nchunk > 1) snprintf(chunks, sizeof chunks, "; %d chunks of at most %d problems", nchunk, kTiledMaxBatch);
-    return snprintf(buf, len, "tiled: %s; %d row block%s of %d rows; %s%s%s; workspace %zu bytes", sweep, R,
-                    R == 1 ? "" : "s", RBS, mrg, compact ? "; the running list rebuilt after stops" : "", chunks,
+    return snprintf(buf, len, "tiled: %s; %d row block%s of %d rows; %s%s%s%s; workspace %zu bytes", sweep, R,
+                    R == 1 ? "" : "s", RBS, mrg, compact ? "; the running list rebuilt after stops" : "",
+                    split ? "; a cost that the device finds to split over two axes: sk_sep_solve instead" : "", chunks,
                     L.total);
 }
 
