@@ -54,6 +54,9 @@ __device__ __forceinline__ float cl_cell(const float *x, const float *y, int D, 
 
 // grad_x: one wavefront per row i (and problem b, or the whole batch for
 // shared clouds); lanes stride over j; D <= kPointsGradD accumulators per lane.
+// grad_y is the same kernel with the roles of the clouds swapped (a kernel of
+// its own, one lane per column running down all the rows, took 1134 us for one
+// pair of 2000 points where this takes 29).
 __global__ __launch_bounds__(kPtThreads) void sk_points_grad_x(PointsBwdArgs A) {
     const int lane = threadIdx.x & 63;
     const size_t wid = (size_t)blockIdx.x * (kPtThreads / 64) + (threadIdx.x >> 6);
@@ -89,45 +92,6 @@ __global__ __launch_bounds__(kPtThreads) void sk_points_grad_x(PointsBwdArgs A) 
         const float v = wave_sum(acc[k]);
         if (k < D && lane == 0) A.grad_X[wid * D + k] = v;
     }
-}
-
-// grad_y: lanes = 64 columns j (one wavefront per column block and problem,
-// or the whole batch for shared clouds); rows summed in order.
-__global__ __launch_bounds__(kPtThreads) void sk_points_grad_y(PointsBwdArgs A) {
-    const int lane = threadIdx.x & 63;
-    const int JB = (A.d2 + 63) / 64;
-    const size_t wid = (size_t)blockIdx.x * (kPtThreads / 64) + (threadIdx.x >> 6);
-    const size_t nw = (size_t)(A.batched ? A.B : 1) * JB;
-    if (wid >= nw) return;
-    const int bx = (int)(wid / JB);
-    const int j = (int)(wid % JB) * 64 + lane;
-    if (j >= A.d2) return;
-    const int D = A.D;
-    const float *y = A.Y + ((size_t)bx * A.d2 + j) * D;
-    float acc[kPointsGradD];
-#pragma unroll
-    for (int k = 0; k < kPointsGradD; ++k) acc[k] = 0.f;
-    const int b0 = A.batched ? bx : 0, b1 = A.batched ? bx + 1 : A.B;
-    for (int b = b0; b < b1; ++b) {
-        const float g = 2.f * A.grad_loss[b];
-        const float bj = A.beta[(size_t)b * A.d2 + j] * kLog2e;
-        const float *Xb = A.X + (size_t)bx * A.d1 * D;
-        float part[kPointsGradD];
-#pragma unroll
-        for (int k = 0; k < kPointsGradD; ++k) part[k] = 0.f;
-        for (int i = 0; i < A.d1; ++i) {
-            const float *x = Xb + (size_t)i * D;
-            const float p = ex2(__builtin_fmaf(A.alpha[(size_t)b * A.d1 + i], kLog2e, bj) + cl_cell(x, y, D, A.rs));
-#pragma unroll
-            for (int k = 0; k < kPointsGradD; ++k)
-                if (k < D) part[k] = __builtin_fmaf(p, y[k] - x[k], part[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < kPointsGradD; ++k) acc[k] = __builtin_fmaf(g, part[k], acc[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < kPointsGradD; ++k)
-        if (k < D) A.grad_Y[((size_t)bx * A.d2 + j) * D + k] = acc[k];
 }
 
 // One side's point gradient for per-sample clouds, as a sweep over that
@@ -238,7 +202,10 @@ void grad_sweep_side(const PointsBwdArgs &a, bool side_x, hipStream_t st) {
     g.out = side_x ? a.grad_X : a.grad_Y;
     g.nr = side_x ? a.d1 : a.d2;
     g.nc = side_x ? a.d2 : a.d1;
-    g.RBS = 64;  // 16 rows per wavefront: the columns' registers are loaded once per 16 rows
+    // 16 rows per wavefront (the columns' registers are loaded once for them),
+    // fewer while the batch leaves work-groups missing (512: two per CU).
+    g.RBS = 64;
+    while (g.RBS > 4 && (int64_t)((g.nr + g.RBS - 1) / g.RBS) * a.B < 512) g.RBS /= 2;
     g.rs = a.rs;
     if (a.D == 1) grad_sweep<1>(g, a.B, st);
     else if (a.D == 2) grad_sweep<2>(g, a.B, st);
@@ -257,9 +224,9 @@ hipError_t launch_points_cost(const float *X, const float *Y, float *C, int nb, 
 }
 
 hipError_t launch_points_grads(const PointsBwdArgs &a, hipStream_t st) {
-    // Per-sample clouds with few coordinates: row sweeps with the other side
-    // in registers (both sides at most 2048 points).
-    if (a.batched && a.D <= kPointsMaxD && a.d1 <= kPointsMaxD2 && a.d2 <= kPointsMaxD2 && a.B <= 65535) {
+    // Per-sample clouds (or one pair) with few coordinates: row sweeps with the
+    // other side in registers (both sides at most 2048 points).
+    if ((a.batched || a.B == 1) && a.D <= kPointsMaxD && a.d1 <= kPointsMaxD2 && a.d2 <= kPointsMaxD2 && a.B <= 65535) {
         if (a.grad_X) grad_sweep_side(a, true, st);
         if (a.grad_Y) grad_sweep_side(a, false, st);
         return hipGetLastError();
@@ -271,8 +238,16 @@ hipError_t launch_points_grads(const PointsBwdArgs &a, hipStream_t st) {
         hipLaunchKernelGGL(sk_points_grad_x, dim3((waves + wpb - 1) / wpb), dim3(kPtThreads), 0, st, a);
     }
     if (a.grad_Y) {
-        const size_t waves = nb * ((a.d2 + 63) / 64);
-        hipLaunchKernelGGL(sk_points_grad_y, dim3((waves + wpb - 1) / wpb), dim3(kPtThreads), 0, st, a);
+        PointsBwdArgs t = a;
+        t.X = a.Y;
+        t.Y = a.X;
+        t.alpha = a.beta;
+        t.beta = a.alpha;
+        t.grad_X = a.grad_Y;
+        t.d1 = a.d2;
+        t.d2 = a.d1;
+        const size_t waves = nb * a.d2;
+        hipLaunchKernelGGL(sk_points_grad_x, dim3((waves + wpb - 1) / wpb), dim3(kPtThreads), 0, st, t);
     }
     return hipGetLastError();
 }

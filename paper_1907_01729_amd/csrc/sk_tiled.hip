@@ -78,7 +78,7 @@ struct TiledArgs {
     // of one to stopacc[b] in one 64-bit atomic; the one that completes the
     // count takes the stop decision (see sk_tiled_merge_cols).
     unsigned long long *stopacc;
-    int MS;
+    int MS, merge_rows;
     float fx_cap;     // parts are clamped to [0, fx_cap] (NaN counts as fx_cap)
     double fx_scale;  // fixed-point units per unit of error
     double fx_tol;    // tol in fixed-point units
@@ -243,21 +243,48 @@ __device__ float col_lse_exact(const TiledArgs &T, int b, int j) {
     return m + lg2(s);
 }
 
-// Merge of the row blocks' (max, sumexp) partials of the first v-update
-// (fixed order): beta of iteration 1.
-__global__ __launch_bounds__(kMergeThreads) void sk_tiled_merge_exact(TiledArgs T) {
+// Merge of the row blocks' (max, sumexp) partials of the first v-update: beta
+// of iteration 1.  A work-group takes 64 columns; its 16 wavefronts each run
+// through every 16th row block, several loads in flight, and their pairs are
+// combined in wavefront order.  (One wavefront per 64 columns running through
+// all the row blocks waited for every load in turn: 48 us at 75 row blocks.)
+constexpr int kMergeExactWaves = 16;
+__global__ __launch_bounds__(64 * kMergeExactWaves) void sk_tiled_merge_exact(TiledArgs T) {
     if (splits(T)) return;
-    const int j = blockIdx.x * kMergeThreads + threadIdx.x;
+    __shared__ float pm[kMergeExactWaves][64], ps[kMergeExactWaves][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int j = blockIdx.x * kMergeThreads + lane;
     const int b = blockIdx.y;
-    if (j >= T.d2) return;
+    const bool in = j < T.d2;
+    float M = kNegBig, S = 0.f;
+    constexpr int U = 4;
+    for (int r0 = w; r0 < T.R; r0 += U * kMergeExactWaves) {
+        float m[U], s[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int r = r0 + q * kMergeExactWaves;
+            const bool ok = in && r < T.R;
+            m[q] = ok ? T.part[pidx(T, 0, r, b, j)] : kNegBig;
+            s[q] = ok ? T.part[pidx(T, 1, r, b, j)] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const float mn = fmaxf(M, m[q]);
+            S = S * ex2(M - mn) + s[q] * ex2(m[q] - mn);
+            M = mn;
+        }
+    }
+    pm[w][lane] = M;
+    ps[w][lane] = S;
+    __syncthreads();
+    if (w != 0 || !in) return;
+    const int n = min(T.R, kMergeExactWaves);
+    for (int q = 1; q < n; ++q) M = fmaxf(M, pm[q][lane]);
+    S = 0.f;
+    for (int q = 0; q < n; ++q) S += ps[q][lane] * ex2(pm[q][lane] - M);
     const float nuj = T.nu[(size_t)b * T.d2 + j];
-    float bnew = neg_inf();
-    float M = kNegBig;
-    for (int r = 0; r < T.R; ++r) M = fmaxf(M, T.part[pidx(T, 0, r, b, j)]);
-    float S = 0.f;
-    for (int r = 0; r < T.R; ++r) S += T.part[pidx(T, 1, r, b, j)] * ex2(T.part[pidx(T, 0, r, b, j)] - M);
-    if (nuj > 0.f) bnew = log2f(nuj) - (M + lg2(S));
-    T.bbuf[(size_t)1 * T.B * T.d2p + (size_t)b * T.d2p + j] = bnew;
+    T.bbuf[(size_t)1 * T.B * T.d2p + (size_t)b * T.d2p + j] =
+        nuj > 0.f ? log2f(nuj) - (M + lg2(S)) : neg_inf();
 }
 
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -289,6 +316,25 @@ __device__ void relist_running(const TiledArgs &T) {
         __syncthreads();
     }
     if (threadIdx.x == 0) *T.nlive = base;
+}
+
+// The stop decision of problem b after iterate k from this work-group's part
+// of its marginal error (one thread per slice; see sk_tiled_merge_cols).
+__device__ __forceinline__ void take_stop(const TiledArgs &T, int b, int k, float err) {
+    bool stop = err <= T.tol;
+    if (T.MS > 1) {
+        const float part = err <= T.fx_cap ? err : T.fx_cap;  // NaN -> fx_cap
+        const unsigned long long add =
+            (1ull << kFxCountShift) + (unsigned long long)__builtin_rint((double)part * T.fx_scale);
+        const unsigned long long got = atomicAdd(T.stopacc + b, add) + add;
+        if ((got >> kFxCountShift) != (unsigned long long)T.MS) return;
+        T.stopacc[b] = 0;  // for the next merge (a later launch)
+        stop = (double)(got & ((1ull << kFxCountShift) - 1ull)) <= T.fx_tol;
+    }
+    if (stop) {
+        T.state[b] = k;
+        if (T.order) atomicAdd(&T.sync[0], 1);
+    }
 }
 
 // Merge after sweep k (k < n_iter), work-group (b, slice) for problem b's
@@ -366,20 +412,65 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
     }
     err = block_sum_n<NT>(err, red);
     if (threadIdx.x != 0) return;
-    bool stop = err <= T.tol;
-    if (T.MS > 1) {
-        const float part = err <= T.fx_cap ? err : T.fx_cap;  // NaN -> fx_cap
-        const unsigned long long add =
-            (1ull << kFxCountShift) + (unsigned long long)__builtin_rint((double)part * T.fx_scale);
-        const unsigned long long got = atomicAdd(T.stopacc + b, add) + add;
-        if ((got >> kFxCountShift) != (unsigned long long)T.MS) return;
-        T.stopacc[b] = 0;  // for the next merge (a later launch)
-        stop = (double)(got & ((1ull << kFxCountShift) - 1ull)) <= T.fx_tol;
+    take_stop(T, b, k, err);
+}
+
+// The same where a problem has many row blocks (few problems, so many blocks
+// for each): a work-group takes 64 columns, 16 threads of 4 columns by 16 row
+// groups; row group q sums every 16th row block, the groups are added in order.
+// The slices of a problem then are ceil(d2 / 64), and the longest chain of
+// loads R / 16 (sk_tiled_merge_cols: R, in steps of 16).  Measured on 8
+// problems of 784 columns with 392 row blocks: 25 us there.
+template <int NT>
+__global__ __launch_bounds__(NT) void sk_tiled_merge_rows(TiledArgs T, int k) {
+    static_assert(NT == 256, "16 columns groups by 16 row groups");
+    __shared__ f4v part[16][17];
+    const int b = blockIdx.x, sl = blockIdx.y;
+    if (b == T.B) {  // the relist work-group of a compacted batch
+        if (sl != 0) return;
+        const int seen = T.sync[0];
+        if (seen == 0) return;
+        relist_running<NT>(T);
+        if (threadIdx.x == 0) atomicSub(&T.sync[0], seen);
+        return;
     }
-    if (stop) {
-        T.state[b] = k;
-        if (T.order) atomicAdd(&T.sync[0], 1);
+    if (T.state[b] != 0) return;  // block-uniform
+    const size_t rstride = (size_t)T.B * T.d2p / 4;  // one row block, in f4v
+    const int cq = threadIdx.x & 15, rq = threadIdx.x >> 4;
+    const f4v *col = reinterpret_cast<const f4v *>(T.part + pidx(T, 0, 0, b, 64 * sl + 4 * cq));  // padded rows
+    f4v cs = {0.f, 0.f, 0.f, 0.f};
+    for (int r0 = rq; r0 < T.R; r0 += 16 * 8) {
+        f4v v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            v[q] = r0 + 16 * q < T.R ? col[(size_t)(r0 + 16 * q) * rstride] : f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) cs += v[q];
     }
+    part[rq][cq] = cs;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x, j = 64 * sl + lane;
+    float err = 0.f, v = 0.f;  // padding columns keep 0
+    if (j < T.d2) {
+        float c = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) c += part[q][lane >> 2][lane & 3];
+        const float nuj = T.nu[(size_t)b * T.d2 + j];
+        const float bold = T.bbuf[(size_t)(k & 1) * T.B * T.d2p + (size_t)b * T.d2p + j];
+        err = fabsf(c - nuj);
+        v = neg_inf();
+        if (nuj > 0.f)
+            v = c >= kSumLo && c <= kSumHi ? bold + log2f(nuj) - lg2(c) : log2f(nuj) - col_lse_exact(T, b, j);
+    }
+    T.bbuf[(size_t)((k + 1) & 1) * T.B * T.d2p + (size_t)b * T.d2p + j] = v;
+    if (!(T.tol > 0.f)) return;
+    if (sl == 0) {
+        const float *re = T.rowerr + (size_t)(k & 1) * T.R * T.B;
+        for (int q = lane; q < T.R; q += 64) err += re[(size_t)q * T.B + b];
+    }
+    err = wave_sum(err);
+    if (lane == 0) take_stop(T, b, k, err);
 }
 
 // Cost of this lane's columns j = lane + 64 c of one row, read from global
@@ -1536,12 +1627,17 @@ __global__ __launch_bounds__(NT) void sk_tiled_final(TiledArgs T) {
         T.alpha_out[u] = aplane(T, K)[u] * kLn2;
     }
     colerr = block_sum_n<NT>(colerr, red);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
+        // The row blocks' scalars: every 64th per lane, then the lanes (one
+        // thread running through them all took 8 us at 75 row blocks).
         float re = 0.f, lo = 0.f;
-        for (int r = 0; r < T.R; ++r) {
+        for (int r = threadIdx.x; r < T.R; r += 64) {
             re += T.rowerr[((size_t)2 * T.R + r) * T.B + b];
             lo += T.lossp[(size_t)r * T.B + b];
         }
+        re = wave_sum(re);
+        lo = wave_sum(lo);
+        if (threadIdx.x != 0) return;
         T.loss_out[b] = -lo / T.s;
         T.merr_out[b] = re + colerr;
         T.iters_out[b] = K;
@@ -1559,12 +1655,16 @@ int tiled_kind(int d2, int c_batched) {
 }
 
 // Which sweep serves a problem: the shared-cost sweep with W problems per
-// work-group when C is shared and the batch fills at least four wavefronts,
-// otherwise one problem per work-group.
-int shared_width(int B, int kind) {
+// work-group when C is shared and the batch fills at least four wavefronts, or
+// the rows are wider than 2048, otherwise one problem per work-group.  (The
+// widest one-problem sweep keeps a quarter of its row in accumulation
+// registers and loads the cost beside the arithmetic: one problem of 4096 x
+// 4096 took 84 us per iteration, in the shared-cost sweep, three wavefronts of
+// four idle, 35.  At 1600 columns it is 14.1 against 17.4.)
+int shared_width(int B, int d2, int kind) {
     if (kind != kKindShared) return 0;
     if (B >= 8) return 8;
-    if (B >= 4) return 4;
+    if (B >= 4 || d2 > 2048) return 4;
     return 0;
 }
 
@@ -1576,12 +1676,16 @@ bool stream_shape(int d2, int kind);
 int stream_waves(int d2);
 
 void row_blocks(int B, int d1, int d2, int kind, int *R, int *RBS) {
-    const int W = shared_width(B, kind);
+    const int W = shared_width(B, d2, kind);
     int want, unit;
     if (stream_shape(d2, kind)) {
-        // Streaming sweep: about one work-group per CU, and at most
-        // 64 kSegs rows per wavefront (row potentials held in registers).
-        want = (256 + B - 1) / (B > 0 ? B : 1);
+        // Streaming sweep: about one work-group per CU, and at most 64 kSegs
+        // rows per wavefront (row potentials held in registers).  Where the
+        // ring leaves no room for a second work-group (above 1024 columns),
+        // never more than the CUs: the 264 of 24 problems of 1024 x 2048 ran
+        // as two rounds, 65 us per iteration, 240 take 41.
+        want = (d2 > 1024 ? 256 : 256 + B - 1) / (B > 0 ? B : 1);
+        want = want < 1 ? 1 : want;
         const int minR = (d1 + 64 * kSegs * stream_waves(d2) - 1) / (64 * kSegs * stream_waves(d2));
         want = want < minR ? minR : want;
         unit = 1;
@@ -1590,6 +1694,10 @@ void row_blocks(int B, int d1, int d2, int kind, int *R, int *RBS) {
         const int target = d2 > 1024 ? 256 : 512;
         want = (target + G - 1) / G;
         want = (want + 7) / 8 * 8;
+        // Rows are reduced in batches (8 per staged chunk up to 1024 columns,
+        // 4 above): a smaller block costs the same and adds a partial.
+        const int least = d2 > 1024 ? 4 : 8, most = (d1 + least - 1) / least;
+        want = want > most ? most : want;
         unit = 1;
     } else if (kind == kKindWide) {
         // Wide rows: ~512 row blocks over the batch, at most 64 per problem
@@ -1640,6 +1748,8 @@ int padded_width(int d2, int kind) {
     return w;
 }
 
+// Row blocks above which the merge splits them too (sk_tiled_merge_rows).
+bool merge_by_rows(int R) { return R >= 32; }
 // Work-groups per problem of the merge after a sweep (4 columns per thread).
 int merge_slices(int d2) { return (d2 + 4 * kMergeColsThreads - 1) / (4 * kMergeColsThreads); }
 
@@ -1694,8 +1804,11 @@ void launch_col_exact(const TiledArgs &T, hipStream_t st) {
 // MS = ceil(d2 / 1024) work-groups of 256 threads per problem, plus the relist
 // work-group of a compacted batch.
 void launch_merge(const TiledArgs &T, int k, hipStream_t st) {
-    hipLaunchKernelGGL(sk_tiled_merge_cols<kMergeColsThreads>, dim3(T.B + (T.order ? 1 : 0), T.MS),
-                       dim3(kMergeColsThreads), 0, st, T, k);
+    const dim3 grid(T.B + (T.order ? 1 : 0), T.MS);
+    if (T.merge_rows)
+        hipLaunchKernelGGL(sk_tiled_merge_rows<kMergeColsThreads>, grid, dim3(kMergeColsThreads), 0, st, T, k);
+    else
+        hipLaunchKernelGGL(sk_tiled_merge_cols<kMergeColsThreads>, grid, dim3(kMergeColsThreads), 0, st, T, k);
 }
 void launch_final(const TiledArgs &T, hipStream_t st) {
     if (T.d2 > 1024)
@@ -1712,7 +1825,7 @@ hipError_t run_wide(const TiledArgs &T, hipStream_t st) {
     hipLaunchKernelGGL(sk_tiled_init, dim3(512), blk, 0, st, T);
     if (T.n_iter > 0) {
         launch_col_exact(T, st);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(kMergeThreads), 0, st, T);
+        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
         for (int k = 1; k <= T.n_iter; ++k) {
             hipLaunchKernelGGL(sk_wide_rows<false>, rg, rblk, 0, st, T, k);
             hipLaunchKernelGGL(sk_wide_cols<false>, cg, blk, 0, st, T, k);
@@ -1737,8 +1850,7 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             if (e != hipSuccess) return e;
         }
         launch_col_exact(T, st);
-        const dim3 mblk(kMergeThreads);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), mblk, 0, st, T);
+        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
         for (int k = 1; k <= T.n_iter; ++k) {
             sweep(k);
             if (k < T.n_iter) launch_merge(T, k, st);
@@ -1772,7 +1884,7 @@ hipError_t run_stream(const TiledArgs &T, hipStream_t st) {
     hipLaunchKernelGGL(sk_tiled_init, dim3(512), dim3(kThreads), 0, st, T);
     if (T.n_iter > 0) {
         launch_col_exact(T, st);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(kMergeThreads), 0, st, T);
+        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
         for (int k = 1; k <= T.n_iter; ++k)
             hipLaunchKernelGGL((sk_tiled_sweep_stream<NC4, false>), grid, blk, lds, st, T, k);
     }
@@ -1904,8 +2016,13 @@ TiledArgs tiled_args(const FwdArgs &a, int kind, void *ws, Layout *Lout) {
     T.nlive = nullptr;
     T.sep_mode = nullptr;
     T.sep = nullptr;
-    T.MS = merge_slices(a.d2);
-    T.stopacc = T.MS > 1 ? reinterpret_cast<unsigned long long *>(base + L.stopacc) : nullptr;
+    T.merge_rows = merge_by_rows(R);
+    T.MS = T.merge_rows ? (a.d2 + 63) / 64 : merge_slices(a.d2);
+    // A merge in slices has its accumulators in their own region, else in the
+    // loss partials' (8 bytes per problem of at least 4 R; they are written
+    // after the last merge).
+    T.stopacc = reinterpret_cast<unsigned long long *>(base + (merge_slices(a.d2) > 1 ? L.stopacc : L.lossp));
+    if (T.MS <= 1) T.stopacc = nullptr;
     // Fixed point of the split merge's stop test: parts clamped to
     // fx_cap = 2^p >= max(8, 2 tol) at 2^(48 - p - ceil(log2 MS)) units per
     // unit of error, so that the sum of MS parts stays below 2^48 and never
@@ -1965,7 +2082,7 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
     if (kind == kKindWide) return run_wide(T, st);
     char *base = static_cast<char *>(ws);
     const int ncw = (a.d2 + 63) / 64;
-    const int W = shared_width(a.B, a.c_batched);
+    const int W = shared_width(a.B, a.d2, a.c_batched);
     // 16-byte global->LDS copies need 16-byte aligned cost rows.
     const bool vec4 = a.d2 % 4 == 0 && ((uintptr_t)a.C % 16) == 0;
     // Early stop with W problems per work-group: compact the running
@@ -1974,14 +2091,14 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
         T.order = reinterpret_cast<int32_t *>(base + L.order);
         T.nlive = T.order + a.B;
     }
-    // A shared cost that may split over two axes: the tables lie in the second
-    // plane of the column partials, which only the exact first v-update of the
-    // sweeps uses, the mode beside the stop counters.
+    // A shared cost that may split over two axes: the tables take the place of
+    // the column partials (if it does not split, they are not read again), the
+    // mode lies beside the stop counters.
     SepArgs sep;
     if (kind == kKindShared && a.n_iter > 0 &&
-        separable_plan(a.B, a.d1, a.d2, a.n_iter, sizeof(float) * (size_t)T.R * T.B * T.d2p, &sep)) {
+        separable_plan(a.B, a.d1, a.d2, a.n_iter, sizeof(float) * 2 * (size_t)T.R * T.B * T.d2p, &sep)) {
         sep.mode = T.sync + 1;
-        sep.table = T.part + (size_t)T.R * T.B * T.d2p;
+        sep.table = T.part;
         sep.mu = T.mu;
         sep.nu = T.nu;
         sep.C = T.C;
@@ -2035,7 +2152,7 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
     const int kind = tiled_kind(a.d2, a.c_batched);
     int R, RBS, JC;
     const Layout L = layout(B, a.d1, a.d2, kind, &R, &RBS, &JC);
-    const int W = shared_width(B, kind), ncw = ncw_bucket(a.d2);
+    const int W = shared_width(B, a.d2, kind), ncw = ncw_bucket(a.d2);
     char sweep[192];
     bool merge = true;
     if (kind == kKindWide) {
@@ -2056,14 +2173,16 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
         snprintf(sweep, sizeof sweep, "sk_tiled_sweep<%d> (one problem per work-group)", ncw);
     }
     char mrg[128];
+    const int slices = merge_by_rows(R) ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     if (merge)
-        snprintf(mrg, sizeof mrg, "sk_tiled_merge_cols<%d> after each sweep (%d work-group%s per problem)",
-                 kMergeColsThreads, merge_slices(a.d2), merge_slices(a.d2) == 1 ? "" : "s");
+        snprintf(mrg, sizeof mrg, "%s<%d> after each sweep (%d work-group%s per problem)",
+                 merge_by_rows(R) ? "sk_tiled_merge_rows" : "sk_tiled_merge_cols", kMergeColsThreads, slices,
+                 slices == 1 ? "" : "s");
     else
         snprintf(mrg, sizeof mrg, "the merge folded into the next sweep");
     SepArgs sep;
     const bool split = kind == kKindShared && a.n_iter > 0 &&
-                       separable_plan(B, a.d1, a.d2, a.n_iter, sizeof(float) * (size_t)R * B * padded_width(a.d2, kind), &sep);
+                       separable_plan(B, a.d1, a.d2, a.n_iter, sizeof(float) * 2 * (size_t)R * B * padded_width(a.d2, kind), &sep);
     const bool compact = W && a.tol > 0.f && a.select != SK_SELECT_NO_COMPACTION;
     const int nchunk = (a.B + kTiledMaxBatch - 1) / kTiledMaxBatch;
     char chunks[64] = "";
