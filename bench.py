@@ -412,6 +412,20 @@ def main():
             roof = dict(bound="hbm", achieved=round(achieved, 2), peak=PEAK_HBM_GBS, unit="GB/s",
                         frac=round(achieved / PEAK_HBM_GBS, 4), kernel=kname, kernel_ms=round(kernel_ms, 5),
                         work="cost bytes read per sweep = 4*B*d1*d2")
+        elif "sk_sep_solve" in sk.sinkhorn_describe(prob.B, prob.d1, prob.d2, 0, prob.lam, prob.n_iter, prob.tol,
+                                                    args.select):
+            # The image and grid workloads: the squared distance on a square
+            # grid splits over the axes, so an iteration is four sets of line
+            # sums (2 side d cells each way, one fused multiply-add per cell)
+            # in one kernel, plus the sweep's and the merge's launches that
+            # find every problem solved.
+            kname = "sk_sep_solve"
+            src = kernel_source_hash(["sk_separable.hip", "sk_device.h"])
+            side = round(prob.d1 ** 0.5)
+            achieved = 2.0 * 4.0 * side * prob.d1 * prob.B / (kernel_ms * 1e-3) / 1e12
+            roof = dict(bound="alu", achieved=round(achieved, 4), peak=PEAK_FP32_VALU, unit="TFLOP/s",
+                        frac=round(achieved / PEAK_FP32_VALU, 4), kernel=kname + " + two launches with nothing to do",
+                        kernel_ms=round(kernel_ms, 5), work="fp32 flops per iteration = 8*B*side*d1 (line sums)")
         else:
             # A shared cost's iteration is the sweep plus the merge of its
             # row-block partials (a short launch that also takes the stop

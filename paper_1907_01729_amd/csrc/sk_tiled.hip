@@ -48,6 +48,23 @@ constexpr int kFxCountShift = 49;       // split merge's stop accumulator: count
 constexpr float kPadCost = -1.0e30f;  // cost of cells beyond d2: plan entry 0, finite so 0*cl = 0
 constexpr float kNegBig = -1.0e30f;   // finite "minus infinity" seed of the online max
 
+// The plain form of a shared cost (sk_tiled_plain.h).
+constexpr int32_t kPlainState = -1;
+constexpr float kPlainLo = 7.8886090522101181e-31f, kPlainHi = 1.2676506002282294e30f;  // 2^-100, 2^100
+constexpr float kPlainSpan = 64.f;
+
+// Device state: range[0], range[1] = order-preserving integers of the cost's
+// smallest and largest entry, range[2] = 1 when the plain form is taken.
+struct PlainArgs {
+    int32_t *range;   // null: not asked
+    float *K, *Kt;    // [p1][p2], [p2][p1], rows of l2 and l1 floats
+    float *Ut, *Vt;   // [p1][pb], [p2][pb], rows of lb floats
+    float *mut, *nut;  // the masses in the same order
+    int32_t *bad;     // [B] problems to solve again
+    int p1, p2, pb;   // padded d1, d2, B
+    int l1, l2, lb;   // their row strides
+};
+
 struct TiledArgs {
     const float *mu, *nu, *C;
     // Point clouds instead of C (C is then null): X [B, d1, D], Y [B, d2, D];
@@ -90,6 +107,7 @@ struct TiledArgs {
     // arguments of its kernels.
     const int32_t *sep_mode;
     const SepArgs *sep;
+    PlainArgs plain;
     int d2p;  // row stride of bbuf and part: d2 rounded up to the sweep's column width
               // (entries past d2 stay 0), so sweeps load and store whole rows unmasked
     float s, tol;
@@ -116,6 +134,8 @@ __device__ __forceinline__ float block_sum_n(float v, float *red) {
 }
 __device__ __forceinline__ float block_sum(float v, float *red) { return block_sum_n<kThreads>(v, red); }
 
+#include "sk_tiled_plain.h"
+
 __global__ __launch_bounds__(kThreads) void sk_tiled_init(TiledArgs T) {
     const size_t n = (size_t)T.B * T.d1;
     for (size_t u = (size_t)blockIdx.x * kThreads + threadIdx.x; u < n; u += (size_t)gridDim.x * kThreads)
@@ -135,6 +155,11 @@ __global__ __launch_bounds__(kThreads) void sk_tiled_init(TiledArgs T) {
         if (T.stopacc) T.stopacc[u] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (T.plain.range) {
+            T.plain.range[0] = 0x7fffffff;
+            T.plain.range[1] = (int32_t)0x80000000;
+            T.plain.range[2] = T.plain.range[3] = 0;
+        }
         T.sync[0] = 0;
         if (T.nlive) *T.nlive = T.B;
     }
@@ -185,7 +210,7 @@ __device__ __forceinline__ float cl_at(const TiledArgs &T, const float *Cb, int 
 // no scalar load.
 template <int W>
 __global__ __launch_bounds__(kMergeThreads) void sk_tiled_col_exact(TiledArgs T) {
-    if (splits(T)) return;  // every problem is solved, its results are out
+    if (splits(T) || plain_taken(T)) return;  // every problem is solved, or takes the plain form
     const int lane = threadIdx.x;
     const int j = blockIdx.x * kMergeThreads + lane;
     const int r = blockIdx.y, b0 = blockIdx.z * W;
@@ -250,7 +275,7 @@ __device__ float col_lse_exact(const TiledArgs &T, int b, int j) {
 // all the row blocks waited for every load in turn: 48 us at 75 row blocks.)
 constexpr int kMergeExactWaves = 16;
 __global__ __launch_bounds__(64 * kMergeExactWaves) void sk_tiled_merge_exact(TiledArgs T) {
-    if (splits(T)) return;
+    if (splits(T) || plain_taken(T)) return;
     __shared__ float pm[kMergeExactWaves][64], ps[kMergeExactWaves][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = blockIdx.x * kMergeThreads + lane;
@@ -357,9 +382,10 @@ __device__ __forceinline__ void take_stop(const TiledArgs &T, int b, int k, floa
 // With a compacted batch, stops are counted in sync[0], and one extra
 // work-group (index B, slice 0) rebuilds the running list from the stops of
 // earlier launches when the count is nonzero.
-template <int NT>
+template <int NT, bool PLAIN>
 __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
     __shared__ float red[NT / 64];
+    extern __shared__ float lds[];
     const int b = blockIdx.x, sl = blockIdx.y;
     if (b == T.B) {  // the relist work-group of a compacted batch
         if (sl != 0) return;
@@ -369,7 +395,11 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
         if (threadIdx.x == 0) atomicSub(&T.sync[0], seen);
         return;
     }
-    if (T.state[b] != 0) return;  // block-uniform
+    const int st = T.state[b];
+    if (st != 0) {  // block-uniform
+        if (PLAIN && st == kPlainState) plain_v<NT / 64>(T, lds, sl * T.B + b, T.MS * T.B);
+        return;
+    }
     const size_t rstride = (size_t)T.B * T.d2p / 4;  // one row block, in f4v
     float err = 0.f;
     const int j0 = 4 * (sl * NT + (int)threadIdx.x);
@@ -421,10 +451,11 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
 // The slices of a problem then are ceil(d2 / 64), and the longest chain of
 // loads R / 16 (sk_tiled_merge_cols: R, in steps of 16).  Measured on 8
 // problems of 784 columns with 392 row blocks: 25 us there.
-template <int NT>
+template <int NT, bool PLAIN>
 __global__ __launch_bounds__(NT) void sk_tiled_merge_rows(TiledArgs T, int k) {
     static_assert(NT == 256, "16 columns groups by 16 row groups");
     __shared__ f4v part[16][17];
+    extern __shared__ float lds[];
     const int b = blockIdx.x, sl = blockIdx.y;
     if (b == T.B) {  // the relist work-group of a compacted batch
         if (sl != 0) return;
@@ -434,7 +465,11 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_rows(TiledArgs T, int k) {
         if (threadIdx.x == 0) atomicSub(&T.sync[0], seen);
         return;
     }
-    if (T.state[b] != 0) return;  // block-uniform
+    const int st = T.state[b];
+    if (st != 0) {  // block-uniform
+        if (PLAIN && st == kPlainState) plain_v<NT / 64>(T, lds, sl * T.B + b, T.MS * T.B);
+        return;
+    }
     const size_t rstride = (size_t)T.B * T.d2p / 4;  // one row block, in f4v
     const int cq = threadIdx.x & 15, rq = threadIdx.x >> 4;
     const f4v *col = reinterpret_cast<const f4v *>(T.part + pidx(T, 0, 0, b, 64 * sl + 4 * cq));  // padded rows
@@ -1016,8 +1051,15 @@ __device__ __forceinline__ float lane_get(float v, int src) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
 }
 
-template <int NCW, int W, int RS, int RB, bool VEC4, bool STATS>
-__global__ __launch_bounds__(64 * W) void sk_tiled_sweep_shared(TiledArgs T, int k) {
+// PLAIN: a batch that may take the plain form (sk_tiled_plain.h), whose products
+// then run in this launch; the wavefronts per SIMD that the sweep's own
+// registers allow are stated, so that the products beside it cost none.
+constexpr int shared_occupancy(int NCW, int W) {
+    return NCW <= 4 ? 8 : NCW <= 8 ? 6 : NCW <= 16 ? 4 : NCW <= 32 || W == 8 ? 2 : 1;
+}
+
+template <int NCW, int W, int RS, int RB, bool VEC4, bool STATS, bool PLAIN>
+__global__ __launch_bounds__(64 * W, PLAIN ? shared_occupancy(NCW, W) : 1) void sk_tiled_sweep_shared(TiledArgs T, int k) {
     constexpr int D2P = NCW * 64;  // LDS row length (columns beyond d2 hold kPadC)
     constexpr int NT = 64 * W;
     constexpr int VW = VEC4 ? 4 : 1;  // floats per lane per global->LDS load
@@ -1040,7 +1082,11 @@ __global__ __launch_bounds__(64 * W) void sk_tiled_sweep_shared(TiledArgs T, int
     const int b = b_raw < T.B ? b_raw : T.B - 1;
     const int st = T.state[b];
     const bool skip = b_raw >= T.B || (!STATS && st != 0);
-    if (!__syncthreads_or(!skip)) return;
+    if (!__syncthreads_or(!skip)) {
+        if (PLAIN && plain_taken(T))
+            plain_u<W>(T, lds, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
+        return;
+    }
 
     // Columns past d2 hold the padding cost (plan entries exactly 0); loads
     // never touch them.  Rows past the block are never read (see below).
@@ -1805,10 +1851,12 @@ void launch_col_exact(const TiledArgs &T, hipStream_t st) {
 // work-group of a compacted batch.
 void launch_merge(const TiledArgs &T, int k, hipStream_t st) {
     const dim3 grid(T.B + (T.order ? 1 : 0), T.MS);
+    const size_t lds = T.plain.range ? sizeof(float) * 1024 * (kMergeColsThreads / 64) : 0;
+    auto go = [&](auto *kernel) { hipLaunchKernelGGL(*kernel, grid, dim3(kMergeColsThreads), lds, st, T, k); };
     if (T.merge_rows)
-        hipLaunchKernelGGL(sk_tiled_merge_rows<kMergeColsThreads>, grid, dim3(kMergeColsThreads), 0, st, T, k);
+        T.plain.range ? go(&sk_tiled_merge_rows<kMergeColsThreads, true>) : go(&sk_tiled_merge_rows<kMergeColsThreads, false>);
     else
-        hipLaunchKernelGGL(sk_tiled_merge_cols<kMergeColsThreads>, grid, dim3(kMergeColsThreads), 0, st, T, k);
+        T.plain.range ? go(&sk_tiled_merge_cols<kMergeColsThreads, true>) : go(&sk_tiled_merge_cols<kMergeColsThreads, false>);
 }
 void launch_final(const TiledArgs &T, hipStream_t st) {
     if (T.d2 > 1024)
@@ -1849,13 +1897,20 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             const hipError_t e = launch_separable(*T.sep, st);
             if (e != hipSuccess) return e;
         }
+        if (T.plain.range) {
+            hipLaunchKernelGGL(sk_plain_range, dim3(128), dim3(256), 0, st, T);
+            hipLaunchKernelGGL(sk_plain_setup, dim3(512), dim3(256), 0, st, T);
+        }
         launch_col_exact(T, st);
         hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
+        if (T.plain.range)
+            hipLaunchKernelGGL(sk_plain_first, dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
         for (int k = 1; k <= T.n_iter; ++k) {
             sweep(k);
             if (k < T.n_iter) launch_merge(T, k, st);
         }
     }
+    if (T.plain.range) hipLaunchKernelGGL(sk_plain_finish, dim3(T.B), dim3(kRedoThreads), 0, st, T);
     stats();
     launch_final(T, st);
     return hipGetLastError();
@@ -1905,17 +1960,22 @@ struct SharedShape {
 template <int NCW, int W, bool VEC4>
 hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
     constexpr int RS = SharedShape<NCW>::RS, RB = SharedShape<NCW>::RB;
-    const size_t lds = sizeof(float) * 2 * RS * NCW * 64;
+    size_t lds = sizeof(float) * 2 * RS * NCW * 64;
+    if (T.plain.range && lds < sizeof(float) * 1024 * W) lds = sizeof(float) * 1024 * W;
     // Chunk buffers above 64 KB need the larger dynamic LDS limit (set on
     // every call: the library keeps no state of its own).
-    hipError_t e = allow_lds(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false>, lds);
-    if (e == hipSuccess) e = allow_lds(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, true>, lds);
-    if (e != hipSuccess) return e;
     const dim3 grid(T.R, (T.B + W - 1) / W), blk(64 * W);
-    return run_sequence(
-        T, st,
-        [&](int k) { hipLaunchKernelGGL((sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false>), grid, blk, lds, st, T, k); },
-        [&]() { hipLaunchKernelGGL((sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, true>), grid, blk, lds, st, T, 0); });
+    auto stats_kernel = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, true, false>;
+    hipError_t e = allow_lds(stats_kernel, lds);
+    if (e != hipSuccess) return e;
+    auto with = [&](auto *kernel) {
+        e = allow_lds(kernel, lds);
+        if (e != hipSuccess) return e;
+        return run_sequence(T, st, [&](int k) { hipLaunchKernelGGL(*kernel, grid, blk, lds, st, T, k); },
+                            [&]() { hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0); });
+    };
+    return T.plain.range ? with(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>)
+                         : with(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, false>);
 }
 
 template <int NCW, int D>
@@ -2016,6 +2076,7 @@ TiledArgs tiled_args(const FwdArgs &a, int kind, void *ws, Layout *Lout) {
     T.nlive = nullptr;
     T.sep_mode = nullptr;
     T.sep = nullptr;
+    T.plain = PlainArgs{};
     T.merge_rows = merge_by_rows(R);
     T.MS = T.merge_rows ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     // A merge in slices has its accumulators in their own region, else in the
@@ -2074,6 +2135,32 @@ hipError_t launch_tiled_points_chunk(const FwdArgs &a, const float *X, const flo
     }
 }
 
+// The plain form of a shared cost, where the batch may take it (the device
+// checks the cost's range).  Both sides measured, in microseconds per
+// iteration: the sweeps as in separable_plan, over padded rows; a product 4.3 and 8.3e-3 per
+// unit of contraction for every 256 tiles of 32 x 32.  The test of the cost,
+// when it fails: 20 and one read of the cost, below 0.5 % of the sweeps.  Rows
+// of up to 256 columns are left out: their sweep has no registers to spare
+// beside the products (3 % slower on a cost out of range).
+bool plain_wanted(const FwdArgs &a, int W, size_t floats, PlainArgs *P) {
+    if (!W || a.d2 <= 256 || a.n_iter < 1 || a.tol > 0.f || a.alpha0 || a.select == SK_SELECT_LOG_ONLY) return false;
+    const double cells = (double)a.d1 * a.d2, sweeps = 10.0 + 64.0 * ncw_bucket(a.d2) * a.d1 * a.B / 4.5e6;
+    if (a.n_iter * sweeps < 200.0 * (20.0 + cells / 1e6)) return false;
+    P->p1 = (a.d1 + 31) / 32 * 32;
+    P->p2 = (a.d2 + 31) / 32 * 32;
+    P->pb = (a.B + 31) / 32 * 32;
+    auto product = [&](int m, int k) {
+        return 4.3 + 8.3e-3 * k * (((size_t)m / 32 * (P->pb / 32) + 255) / 256);
+    };
+    if (product(P->p1, P->p2) + product(P->p2, P->p1) > 0.7 * sweeps) return false;
+    auto stride = [](int n) { return ((n + 63) / 64 | 1) * 64; };
+    P->l1 = stride(P->p1);
+    P->l2 = stride(P->p2);
+    P->lb = stride(P->pb);
+    const size_t need = (size_t)P->p1 * P->l2 + (size_t)P->p2 * P->l1 + 2 * (size_t)(P->p1 + P->p2) * P->lb + a.B;
+    return need <= floats;
+}
+
 // One chunk (at most kTiledMaxBatch problems) of the forward.
 hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
     Layout L;
@@ -2118,6 +2205,19 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
         sep.tol = T.tol;
         T.sep_mode = sep.mode;
         T.sep = &sep;
+    }
+    // The plain form's arrays take the place of the column partials (not used
+    // in its iterations), its flags that of the statistics' row errors.
+    if (kind == kKindShared && T.R * T.B >= 4 && plain_wanted(a, W, 2 * (size_t)T.R * T.B * T.d2p, &T.plain)) {
+        PlainArgs &P = T.plain;
+        P.range = reinterpret_cast<int32_t *>(T.rowerr + 2 * (size_t)T.R * T.B);
+        P.K = T.part;
+        P.Kt = P.K + (size_t)P.p1 * P.l2;
+        P.Ut = P.Kt + (size_t)P.p2 * P.l1;
+        P.Vt = P.Ut + (size_t)P.p1 * P.lb;
+        P.mut = P.Vt + (size_t)P.p2 * P.lb;
+        P.nut = P.mut + (size_t)P.p1 * P.lb;
+        P.bad = reinterpret_cast<int32_t *>(P.nut + (size_t)P.p2 * P.lb);
     }
     if (W == 8) return vec4 ? dispatch_shared<8, true>(T, ncw, st) : dispatch_shared<8, false>(T, ncw, st);
     if (W == 4) return vec4 ? dispatch_shared<4, true>(T, ncw, st) : dispatch_shared<4, false>(T, ncw, st);
@@ -2183,12 +2283,16 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
     SepArgs sep;
     const bool split = kind == kKindShared && a.n_iter > 0 &&
                        separable_plan(B, a.d1, a.d2, a.n_iter, sizeof(float) * 2 * (size_t)R * B * padded_width(a.d2, kind), &sep);
+    PlainArgs plain;
+    const bool prod = kind == kKindShared && R * B >= 4 &&
+                      plain_wanted(a, W, 2 * (size_t)R * B * padded_width(a.d2, kind), &plain);
     const bool compact = W && a.tol > 0.f && a.select != SK_SELECT_NO_COMPACTION;
     const int nchunk = (a.B + kTiledMaxBatch - 1) / kTiledMaxBatch;
     char chunks[64] = "";
     if (nchunk > 1) snprintf(chunks, sizeof chunks, "; %d chunks of at most %d problems", nchunk, kTiledMaxBatch);
-    return snprintf(buf, len, "tiled: %s; %d row block%s of %d rows; %s%s%s%s; workspace %zu bytes", sweep, R,
+    return snprintf(buf, len, "tiled: %s; %d row block%s of %d rows; %s%s%s%s%s; workspace %zu bytes", sweep, R,
                     R == 1 ? "" : "s", RBS, mrg, compact ? "; the running list rebuilt after stops" : "",
+                    prod ? "; a cost that spans at most 64 bits: the plain form as matrix products" : "",
                     split ? "; a cost that the device finds to split over two axes: sk_sep_solve instead" : "", chunks,
                     L.total);
 }

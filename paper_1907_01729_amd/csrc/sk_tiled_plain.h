@@ -1,0 +1,279 @@
+// sk_tiled_plain.h -- the plain form u = mu / (K v), v = nu / (K^T u) on the
+// matrix cores, for large supports with a shared cost (included by
+// sk_tiled.hip; TiledArgs and the helpers it uses are defined there).
+//
+// K = 2^(-s (C - min C)) is the same for the whole batch, so a half-step is a
+// matrix product of K with all the batch's scalings.  It is taken where fp32
+// holds it, by the resident kernels' rule: the scaled cost spans at most 64
+// bits.  Every sum is then within [2^-64, 1] of the sum of its operand's
+// scalings, whose product stays within [1, 2^64]; a sum that leaves [2^-100,
+// 2^100] all the same (it takes masses far from a histogram) marks its problem,
+// which is solved again in the log domain.
+//
+// The launches are those of the sweeps (sweep: u-update, merge: v-update), so
+// a cost out of range costs nothing per iteration: in range, every problem's
+// state is kPlainState and the kernels that would skip a stopped problem run
+// the products instead.
+//
+// fp32 products on v_mfma_f32_32x32x2_f32: a work-group takes 32 rows by 32
+// problems and splits the contraction over its wavefronts, whose partial tiles
+// meet in LDS.  K is kept in both orders and the scalings as [support][batch],
+// all padded with zeros to multiples of 32, so every operand load is two runs
+// of 128 bytes and nothing is masked; rows lie an odd number of 256-byte lines
+// apart, so that a column's rows spread over the L2's channels.  Measured on
+// 256 problems of 1000 x 1000: 12.9 and 13.6 us for the two launches (sweep
+// and merge: 64.6 and 5.8), 4.3 of each the launch, the setup and the merge;
+// the matrix cores alone would take 3.3, the loads of the operands set the pace.
+#pragma once
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ int32_t ordered(float x) {
+    const int32_t i = __float_as_int(x);
+    return i >= 0 ? i : i ^ 0x7fffffff;
+}
+__device__ __forceinline__ float unordered(int32_t i) { return __int_as_float(i >= 0 ? i : i ^ 0x7fffffff); }
+
+// Smallest and largest entry of the cost (a NaN fails the test in plain_taken
+// through range[3]).
+__global__ __launch_bounds__(256) void sk_plain_range(TiledArgs T) {
+    if (splits(T)) return;
+    __shared__ float least[4], most[4];
+    const size_t n = (size_t)T.d1 * T.d2, step = (size_t)gridDim.x * 256;
+    float lo = __builtin_inff(), hi = -__builtin_inff();
+    bool bad = false;
+    for (size_t u = (size_t)blockIdx.x * 256 + threadIdx.x; u < n; u += 8 * step) {
+        float c[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) c[q] = T.C[u + q * step < n ? u + q * step : u];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            lo = fminf(lo, c[q]);
+            hi = fmaxf(hi, c[q]);
+            bad = bad || !(fabsf(c[q]) < __builtin_inff());
+        }
+    }
+    const int w = threadIdx.x >> 6;
+    lo = -wave_max(-lo);
+    hi = wave_max(hi);
+    if ((threadIdx.x & 63) == 0) {
+        least[w] = lo;
+        most[w] = hi;
+    }
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) {  // one pair of atomics per work-group: they meet on one line
+        atomicMin(T.plain.range + 0, ordered(fminf(fminf(least[0], least[1]), fminf(least[2], least[3]))));
+        atomicMax(T.plain.range + 1, ordered(fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3]))));
+        if (bad) atomicOr(T.plain.range + 3, 1);
+    }
+}
+// The decision, the same in every kernel between sk_plain_range and the setup.
+__device__ __forceinline__ bool plain_fits(const TiledArgs &T) {
+    if (splits(T) || T.plain.range[3] != 0) return false;
+    const float lo = unordered(T.plain.range[0]), hi = unordered(T.plain.range[1]);
+    return T.s * (hi - lo) <= kPlainSpan;
+}
+
+// K in both orders, the masses transposed, u = 1 on the support of mu, v = 0,
+// and every problem's state.  Work-groups of 32 x 32 tiles: first K's, then
+// mu's and nu's (the transpose goes through LDS).
+__global__ __launch_bounds__(256) void sk_plain_setup(TiledArgs T) {
+    __shared__ float tile[32][33];
+    if (!plain_fits(T)) return;
+    const PlainArgs &P = T.plain;
+    const float lo = unordered(P.range[0]);
+    const int n1 = P.p1 / 32, n2 = P.p2 / 32, nb = P.pb / 32;
+    const int tiles = n1 * n2 + nb * (n1 + n2);
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const bool cost = t < n1 * n2;
+        const int u = t - n1 * n2;
+        const bool first = u < nb * n1;  // mu's
+        const int v = first ? u : u - nb * n1;
+        // tile (row, column) of a [rows][cols] source: K from C, else a mass [B][d]
+        const int rows = cost ? T.d1 : T.B, cols = cost ? T.d2 : (first ? T.d1 : T.d2);
+        const int nc = cost ? n2 : (first ? n1 : n2);
+        const int r0 = (cost ? t / nc : v / nc) * 32, c0 = (cost ? t % nc : v % nc) * 32;
+        const float *src = cost ? T.C : (first ? T.mu : T.nu);
+        for (int y = ty; y < 32; y += 8) {
+            const int r = r0 + y, c = c0 + tx;
+            float x = 0.f;
+            if (r < rows && c < cols) {
+                x = src[(size_t)r * cols + c];
+                if (cost) {  // 2^(-s (C - lo)), the integer part of the exponent kept apart
+                    const double e = -(double)T.s * ((double)x - (double)lo), f = floor(e);
+                    x = ldexpf(exp2f((float)(e - f)), (int)f);
+                    P.K[(size_t)r * P.l2 + c] = x;
+                }
+            } else if (cost) {
+                P.K[(size_t)r * P.l2 + c] = 0.f;
+            }
+            tile[y][tx] = x;
+        }
+        __syncthreads();
+        for (int y = ty; y < 32; y += 8) {
+            const int r = c0 + y, c = r0 + tx;  // transposed
+            const float x = tile[tx][y];
+            if (cost) {
+                P.Kt[(size_t)r * P.l1 + c] = x;
+            } else {
+                const size_t at = (size_t)r * P.lb + c;
+                (first ? P.mut : P.nut)[at] = x;
+                (first ? P.Ut : P.Vt)[at] = first && x > 0.f ? 1.f : 0.f;
+            }
+        }
+        __syncthreads();
+    }
+    for (int b = blockIdx.x * 256 + threadIdx.x; b < T.B; b += gridDim.x * 256) {
+        T.state[b] = kPlainState;
+        P.bad[b] = 0;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) P.range[2] = 1;
+}
+__device__ __forceinline__ bool plain_taken(const TiledArgs &T) { return T.plain.range && T.plain.range[2] != 0; }
+
+// out[m][n] = mass[m][n] / sum_k A[k][m] X[k][n] over m < M, n < N in tiles of
+// 32 x 32: work-groups wg, wg + nwg, ... of NW wavefronts; lds: NW * 1024
+// floats.  kd is a multiple of 32; out's rows and columns past its size keep
+// 0.  One batch of loads is in flight beside a batch's products: bound by those
+// loads (20 cycles per 256 bytes and CU), so loading further ahead only adds
+// batches that are thrown away (15.2 us with three more, 12.7 so).
+constexpr int kPlainUnroll = 8;  // matrix instructions (2 of the contraction each) per batch of loads
+template <int NW>
+__device__ __forceinline__ void plain_product(const float *A, int lda, const float *X, const float *mass, float *out,
+                                              int ldx, int kd, int M, int N, int32_t *bad, float *lds, int wg,
+                                              int nwg) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Consecutive work-groups go to the 8 XCDs in turn: a row tile stays on one
+    // XCD, whose L2 then keeps its share of K over the iterations.
+    const int nt = (N + 31) / 32, mt = (M + 31) / 32, tiles = (mt + 7) / 8 * 8 * nt;
+    for (int t = wg; t < tiles; t += nwg) {
+        const int mi = (t & 7) + 8 * ((t >> 3) / nt), m0 = mi * 32, n0 = (t >> 3) % nt * 32;
+        if (mi >= mt) continue;  // work-group uniform
+        // This wavefront's batches of the contraction: w, w + NW, ...
+        constexpr int KB = 2 * kPlainUnroll;
+        const float *a = A + (size_t)(lane >> 5) * lda + m0 + (lane & 31);
+        const float *x = X + (size_t)(lane >> 5) * ldx + n0 + (lane & 31);
+        f16v acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float av[kPlainUnroll], xv[kPlainUnroll];
+        auto load = [&](int k) {
+#pragma unroll
+            for (int q = 0; q < kPlainUnroll; ++q) {
+                av[q] = a[(size_t)(k + 2 * q) * lda];
+                xv[q] = x[(size_t)(k + 2 * q) * ldx];
+            }
+        };
+        int k = w * KB;
+        if (k < kd) load(k);
+        for (; k < kd; k += NW * KB) {
+            float ac[kPlainUnroll], xc[kPlainUnroll];
+#pragma unroll
+            for (int q = 0; q < kPlainUnroll; ++q) {
+                ac[q] = av[q];
+                xc[q] = xv[q];
+            }
+            load(k + NW * KB < kd ? k + NW * KB : k);  // the next batch, in flight over this one's products
+#pragma unroll
+            for (int q = 0; q < kPlainUnroll; ++q)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ac[q], xc[q], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)  // row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
+            lds[w * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[r];
+        __syncthreads();
+        for (int u = threadIdx.x; u < 1024; u += 64 * NW) {
+            const int m = m0 + (u >> 5), n = n0 + (u & 31);
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) s += lds[q * 1024 + u];
+            if (m < M && n < N) {
+                const size_t at = (size_t)m * ldx + n;
+                const float mm = mass[at];
+                float v = 0.f;
+                if (mm > 0.f) {
+                    if (!(s >= kPlainLo && s <= kPlainHi)) bad[n] = 1;
+                    v = mm * __builtin_amdgcn_rcpf(s);
+                }
+                out[at] = v;
+            }
+        }
+        __syncthreads();
+    }
+}
+template <int NW>
+__device__ __forceinline__ void plain_u(const TiledArgs &T, float *lds, int wg, int nwg) {
+    const PlainArgs &P = T.plain;
+    plain_product<NW>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, P.bad, lds, wg, nwg);
+}
+template <int NW>
+__device__ __forceinline__ void plain_v(const TiledArgs &T, float *lds, int wg, int nwg) {
+    const PlainArgs &P = T.plain;
+    plain_product<NW>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, P.bad, lds, wg, nwg);
+}
+// The first v-update.
+__global__ __launch_bounds__(512) void sk_plain_first(TiledArgs T) {
+    extern __shared__ float lds[];
+    if (!plain_taken(T)) return;
+    plain_v<8>(T, lds, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// log2 v (-inf at 0) to half a unit in the last place: the hardware's logarithm
+// of the mantissa alone, added to the exponent (of the whole number it is off
+// by a unit of the result, 2e-6 at 2^-20).
+__device__ __forceinline__ float exact_lg2(float v) {
+    return (float)__builtin_amdgcn_frexp_expf(v) + lg2(__builtin_amdgcn_frexp_mantf(v));
+}
+
+// Back to the sweeps' potentials for the closing statistics: a = log2 u,
+// b = log2 v + s min C, the state of a problem that ran all its iterations.
+// A problem out of range is solved here from its start in the log domain, one
+// work-group for all its iterations.
+constexpr int kRedoThreads = 1024;
+__global__ __launch_bounds__(kRedoThreads) void sk_plain_finish(TiledArgs T) {
+    if (!plain_taken(T)) return;
+    const PlainArgs &P = T.plain;
+    const int b = blockIdx.x, d1 = T.d1, d2 = T.d2, n = T.n_iter;
+    float *a = T.a + (size_t)b * d1, *bn = T.bbuf + (size_t)(n & 1) * T.B * T.d2p + (size_t)b * T.d2p;
+    if (threadIdx.x == 0) T.state[b] = 0;
+    if (P.bad[b] == 0) {
+        const float shift = T.s * unordered(P.range[0]);
+        for (int i = threadIdx.x; i < d1; i += kRedoThreads) {
+            const float u = P.Ut[(size_t)i * P.lb + b];
+            a[i] = exact_lg2(u);
+        }
+        for (int j = threadIdx.x; j < d2; j += kRedoThreads) {
+            const float v = P.Vt[(size_t)j * P.lb + b];
+            bn[j] = exact_lg2(v) + shift;
+        }
+        return;
+    }
+    const float *mu = T.mu + (size_t)b * d1, *nu = T.nu + (size_t)b * d2;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int k = 1; k <= n; ++k) {
+        for (int j = threadIdx.x; j < d2; j += kRedoThreads) {
+            float m = kNegBig, s = 0.f;
+            for (int i = 0; i < d1; ++i) {
+                const float x = a[i] - T.s * T.C[(size_t)i * d2 + j], mn = fmaxf(m, x);
+                s = s * ex2(m - mn) + ex2(x - mn);
+                m = mn;
+            }
+            bn[j] = nu[j] > 0.f ? log2f(nu[j]) - (m + lg2(s)) : neg_inf();
+        }
+        __threadfence_block();
+        __syncthreads();
+        for (int i = w; i < d1; i += kRedoThreads / 64) {
+            if (!(mu[i] > 0.f)) continue;
+            float m = kNegBig, s = 0.f;
+            for (int j = lane; j < d2; j += 64) {
+                const float x = bn[j] - T.s * T.C[(size_t)i * d2 + j], mn = fmaxf(m, x);
+                s = s * ex2(m - mn) + ex2(x - mn);
+                m = mn;
+            }
+            const float top = wave_max(m);
+            s = wave_sum(s * ex2(m - top));
+            if (lane == 0) a[i] = log2f(mu[i]) - (top + lg2(s));
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
+}

@@ -1,0 +1,64 @@
+"""GPU parity of the plain form of the tiled regime (a shared cost that spans at
+most 64 bits, products on the matrix cores): sizes around the 32 x 32 tiles,
+zero masses, a cost just outside the range (the sweeps), and a problem whose
+sums leave fp32's guarded range (solved again in the log domain)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1907_01729_amd as sk
+import workloads
+from parity_util import gauge_fixed_errors, loss_rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")
+
+
+def run(mu, nu, C, lam, n_iter, sample):
+    assert "matrix products" in sk.sinkhorn_describe(mu.shape[0], mu.shape[1], nu.shape[1], 0, lam, n_iter)
+    out = {k: v.cpu().numpy() for k, v in sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, n_iter).items()}
+    ref = oracle.forward(mu[sample], nu[sample], C, lam, n_iter)
+    ea, eb = gauge_fixed_errors(mu[sample], nu[sample], out["alpha"][sample], out["beta"][sample], ref["alpha"],
+                                ref["beta"])
+    assert np.all(out["iters"] == n_iter)
+    return out, ref, loss_rel_err(out["loss"][sample], ref["loss"]), max(ea, eb)
+
+
+# Sums of d positive fp32 products: relative error of a potential <= (d + few) 2^-24 in the worst case, a few 2^-24
+# in practice; the potentials (tens of units) are rounded to fp32 at the end.
+LOSS, POT = 2e-6, 2e-5
+
+
+@pytest.mark.parametrize("B, d1, d2, lam, zero", [
+    (224, 640, 640, 0.05, 0.0),    # whole tiles
+    (225, 641, 672, 0.05, 0.1),    # one row, one problem past a tile
+    (255, 607, 801, 0.04, 0.1),    # one short of a tile
+    (100, 1100, 1030, 0.023, 0.0),  # 62.7 bits
+])
+def test_plain_tiled(B, d1, d2, lam, zero):
+    p = workloads.random_problem(41, B, d1, d2, lam, 120, zero_frac=zero)
+    sample = [0, 1, 31, 32, B - 1]
+    _, _, el, ep = run(p.mu, p.nu, p.C, lam, 120, sample)
+    assert el <= LOSS and ep <= POT
+
+
+def test_cost_out_of_range():
+    p = workloads.random_problem(42, 224, 640, 640, 0.0222, 120)  # 65 bits
+    _, _, el, ep = run(p.mu, p.nu, p.C, p.lam, 120, [0, 223])
+    assert el <= 1e-4 and ep <= 1e-3
+
+
+def test_problem_out_of_range():
+    p = workloads.random_problem(43, 224, 640, 640, 0.05, 120)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    mu[7] *= np.float32(2.0 ** 104)  # not a histogram: the sums pass 2^100
+    nu[7] *= np.float32(2.0 ** 104)
+    out, ref, el, ep = run(mu, nu, p.C, p.lam, 120, [0, 6, 8, 223])
+    assert el <= LOSS and ep <= POT
+    one = oracle.forward(mu[7:8], nu[7:8], p.C, p.lam, 120)
+    ea, eb = gauge_fixed_errors(mu[7:8], nu[7:8], out["alpha"][7:8], out["beta"][7:8], one["alpha"], one["beta"])
+    assert max(ea, eb) <= 1e-3 and loss_rel_err(out["loss"][7:8], one["loss"]) <= 1e-4
