@@ -1706,11 +1706,13 @@ int tiled_kind(int d2, int c_batched) {
 // widest one-problem sweep keeps a quarter of its row in accumulation
 // registers and loads the cost beside the arithmetic: one problem of 4096 x
 // 4096 took 84 us per iteration, in the shared-cost sweep, three wavefronts of
-// four idle, 35.  At 1600 columns it is 14.1 against 17.4.)
-int shared_width(int B, int d2, int kind) {
+// four idle, 35.  At 1600 columns it is 14.1 against 17.4.  More rows than 256
+// row blocks of 64 kSegs hold would take more row blocks, and their partials
+// more workspace, than the one-problem sweep.)
+int shared_width(int B, int d1, int d2, int kind) {
     if (kind != kKindShared) return 0;
     if (B >= 8) return 8;
-    if (B >= 4 || d2 > 2048) return 4;
+    if (B >= 4 || (d2 > 2048 && d1 <= 256 * 64 * kSegs)) return 4;
     return 0;
 }
 
@@ -1722,7 +1724,7 @@ bool stream_shape(int d2, int kind);
 int stream_waves(int d2);
 
 void row_blocks(int B, int d1, int d2, int kind, int *R, int *RBS) {
-    const int W = shared_width(B, d2, kind);
+    const int W = shared_width(B, d1, d2, kind);
     int want, unit;
     if (stream_shape(d2, kind)) {
         // Streaming sweep: about one work-group per CU, and at most 64 kSegs
@@ -2169,7 +2171,7 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
     if (kind == kKindWide) return run_wide(T, st);
     char *base = static_cast<char *>(ws);
     const int ncw = (a.d2 + 63) / 64;
-    const int W = shared_width(a.B, a.d2, a.c_batched);
+    const int W = shared_width(a.B, a.d1, a.d2, a.c_batched);
     // 16-byte global->LDS copies need 16-byte aligned cost rows.
     const bool vec4 = a.d2 % 4 == 0 && ((uintptr_t)a.C % 16) == 0;
     // Early stop with W problems per work-group: compact the running
@@ -2252,7 +2254,7 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
     const int kind = tiled_kind(a.d2, a.c_batched);
     int R, RBS, JC;
     const Layout L = layout(B, a.d1, a.d2, kind, &R, &RBS, &JC);
-    const int W = shared_width(B, a.d2, kind), ncw = ncw_bucket(a.d2);
+    const int W = shared_width(B, a.d1, a.d2, kind), ncw = ncw_bucket(a.d2);
     char sweep[192];
     bool merge = true;
     if (kind == kKindWide) {

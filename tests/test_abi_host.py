@@ -168,6 +168,13 @@ def test_points_rejections_on_host():
     assert _fwd_points(p, 3, ptr=0x1000, ws=need - 1) == -5
 
 
+@pytest.mark.parametrize("B", [1, 2, 3])
+@pytest.mark.parametrize("d1", [4096, 65536, 65537, 100000])
+def test_few_wide_problems_fit_the_library_scratch(B, d1):
+    # the row blocks' partials of up to three problems stay within 256 row blocks whatever the rows
+    assert sk.sinkhorn_workspace_bytes(B, d1, 4096, 0, 0.1, 10) <= sk.NOALLOC_SCRATCH_BYTES
+
+
 def test_points_workspace_sizes():
     # on-the-fly sweep (per-sample clouds, tiled shape, D <= 3, d2 <= 2048): no cost matrix in the workspace
     on_the_fly = sk.sinkhorn_points_workspace_bytes(32, 1024, 2048, 1, 3, 0.05, 100)
