@@ -130,6 +130,13 @@ def test_sharp_tiled_shapes(d1, d2):
     check_sharp(prob, max_cg=1000)
 
 
+@pytest.mark.parametrize("d1,d2", [(1024, 131), (1025, 257), (140, 1029), (2049, 130), (4097, 70), (700, 1024)])
+def test_sharp_tiled_update_sizes(d1, d2):
+    """Both sides of the update's sizes (1, 2 or 4 entries per thread, or a loop), ragged row blocks, zero masses."""
+    prob = workloads.random_problem(seed=700 + d1 + d2, B=3, d1=d1, d2=d2, lam=0.2, n_iter=100, zero_frac=0.1)
+    check_sharp(prob, max_cg=1000)
+
+
 def test_sharp_tiled_against_converged_oracle():
     """Both forwards converged (3000 iterations, lambda = 0.2): the GPU's sharp
     gradient from its own forward matches the oracle's from its own."""
