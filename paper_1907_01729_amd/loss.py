@@ -21,11 +21,14 @@ class SinkhornLoss(torch.autograd.Function):
         ctx.lam = lam
         ctx.sharp = sharp
         ctx.mark_non_differentiable(out["alpha"], out["beta"], out["marg_err"], out["iters"])
+        ctx.set_materialize_grads(False)  # no zeros allocated and filled for the four state outputs
         return out["loss"], out["alpha"], out["beta"], out["marg_err"], out["iters"]
 
     @staticmethod
     def backward(ctx, grad_loss, *unused):
         mu, nu, C, alpha, beta = ctx.saved_tensors
+        if grad_loss is None:
+            grad_loss = mu.new_zeros(mu.shape[0])
         want_C = ctx.needs_input_grad[2]
         if ctx.sharp:
             if want_C:
@@ -65,11 +68,14 @@ class SinkhornPointsLoss(torch.autograd.Function):
         ctx.save_for_backward(mu, nu, X, Y, out["alpha"], out["beta"])
         ctx.lam = lam
         ctx.mark_non_differentiable(out["alpha"], out["beta"], out["marg_err"], out["iters"])
+        ctx.set_materialize_grads(False)  # no zeros allocated and filled for the four state outputs
         return out["loss"], out["alpha"], out["beta"], out["marg_err"], out["iters"]
 
     @staticmethod
     def backward(ctx, grad_loss, *unused):
         mu, nu, X, Y, alpha, beta = ctx.saved_tensors
+        if grad_loss is None:
+            grad_loss = mu.new_zeros(mu.shape[0])
         want = ctx.needs_input_grad[2] or ctx.needs_input_grad[3]
         g = sinkhorn_backward_points(grad_loss.contiguous(), mu.contiguous(), nu.contiguous(), X.contiguous(),
                                      Y.contiguous(), ctx.lam, alpha, beta, grad_points=want)
