@@ -50,7 +50,7 @@ constexpr float kNegBig = -1.0e30f;   // finite "minus infinity" seed of the onl
 
 // The plain form of a shared cost (sk_tiled_plain.h).
 constexpr int32_t kPlainState = -1;
-constexpr float kPlainLo = 7.8886090522101181e-31f, kPlainHi = 1.2676506002282294e30f;  // 2^-100, 2^100
+constexpr float kPlainLo = 8.2718061255302767e-25f, kPlainHi = 1.2676506002282294e30f;  // 2^-80, 2^100
 constexpr float kPlainSpan = 64.f;
 
 // Device state: range[0], range[1] = order-preserving integers of the cost's
@@ -59,7 +59,7 @@ struct PlainArgs {
     int32_t *range;   // null: not asked
     float *K, *Kt;    // [p1][p2], [p2][p1], rows of l2 and l1 floats
     float *Ut, *Vt;   // [p1][pb], [p2][pb], rows of lb floats
-    float *mut, *nut;  // the masses in the same order
+    float *mut, *nut;  // the masses in the same order; at the end, the last sums
     int32_t *bad;     // [B] problems to solve again
     int p1, p2, pb;   // padded d1, d2, B
     int l1, l2, lb;   // their row strides
@@ -1912,7 +1912,11 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             if (k < T.n_iter) launch_merge(T, k, st);
         }
     }
-    if (T.plain.range) hipLaunchKernelGGL(sk_plain_finish, dim3(T.B), dim3(kRedoThreads), 0, st, T);
+    if (T.plain.range) {
+        hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
+        hipLaunchKernelGGL((sk_plain_last<4, false>), dim3(512), dim3(256), sizeof(float) * 1024 * 4, st, T);
+        hipLaunchKernelGGL(sk_plain_finish, dim3(T.B), dim3(kRedoThreads), 0, st, T);
+    }
     stats();
     launch_final(T, st);
     return hipGetLastError();
@@ -1970,14 +1974,21 @@ hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
     auto stats_kernel = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, true, false>;
     hipError_t e = allow_lds(stats_kernel, lds);
     if (e != hipSuccess) return e;
-    auto with = [&](auto *kernel) {
-        e = allow_lds(kernel, lds);
-        if (e != hipSuccess) return e;
-        return run_sequence(T, st, [&](int k) { hipLaunchKernelGGL(*kernel, grid, blk, lds, st, T, k); },
-                            [&]() { hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0); });
-    };
-    return T.plain.range ? with(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>)
-                         : with(&sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, false>);
+    // The last sweep beside the plain form runs no product (see sk_plain_last).
+    auto sweep = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, false>;
+    auto both = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>;
+    e = allow_lds(sweep, lds);
+    if (e == hipSuccess && T.plain.range) e = allow_lds(both, lds);
+    if (e != hipSuccess) return e;
+    return run_sequence(
+        T, st,
+        [&](int k) {
+            if (T.plain.range && k < T.n_iter)
+                hipLaunchKernelGGL(*both, grid, blk, lds, st, T, k);
+            else
+                hipLaunchKernelGGL(*sweep, grid, blk, lds, st, T, k);
+        },
+        [&]() { hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0); });
 }
 
 template <int NCW, int D>

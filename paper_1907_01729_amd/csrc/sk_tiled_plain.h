@@ -3,12 +3,20 @@
 // sk_tiled.hip; TiledArgs and the helpers it uses are defined there).
 //
 // K = 2^(-s (C - min C)) is the same for the whole batch, so a half-step is a
-// matrix product of K with all the batch's scalings.  It is taken where fp32
-// holds it, by the resident kernels' rule: the scaled cost spans at most 64
-// bits.  Every sum is then within [2^-64, 1] of the sum of its operand's
-// scalings, whose product stays within [1, 2^64]; a sum that leaves [2^-100,
-// 2^100] all the same (it takes masses far from a histogram) marks its problem,
-// which is solved again in the log domain.
+// matrix product of K with all the batch's scalings.  It is taken where the
+// scaled cost spans at most 64 bits (as in the resident kernels).  Every sum is
+// then within [2^-64, 1] of the sum of its operand's scalings, whose product
+// stays within [1, 2^64]; a sum that leaves [2^-80, 2^100] all the same (it
+// takes masses far from a histogram) marks its problem, which is solved again
+// in the log domain.
+//
+// Scalings are not guarded (the resident kernels guard both): a small mass may
+// give one below 2^-126, where it has few bits or none.  As an operand that
+// does not matter: it is off by less than 2^-126, K <= 1, and the sums it goes
+// into are at least 2^-80, so d of them move a sum by less than d 2^-46 of it.
+// And the returned potentials are not taken from scalings but from the last
+// sums, log2 mass - log2 sum (mass and sum as mantissa and exponent, so that
+// nothing underflows).
 //
 // The launches are those of the sweeps (sweep: u-update, merge: v-update), so
 // a cost out of range costs nothing per iteration: in range, every problem's
@@ -135,11 +143,12 @@ __device__ __forceinline__ bool plain_taken(const TiledArgs &T) { return T.plain
 // out[m][n] = mass[m][n] / sum_k A[k][m] X[k][n] over m < M, n < N in tiles of
 // 32 x 32: work-groups wg, wg + nwg, ... of NW wavefronts; lds: NW * 1024
 // floats.  kd is a multiple of 32; out's rows and columns past its size keep
-// 0.  One batch of loads is in flight beside a batch's products: bound by those
-// loads (20 cycles per 256 bytes and CU), so loading further ahead only adds
-// batches that are thrown away (15.2 us with three more, 12.7 so).
+// 0.  SUMS: out takes the sums (of positive masses) themselves.  One batch of
+// loads is in flight beside a batch's products: bound by those loads (20 cycles
+// per 256 bytes and CU), so loading further ahead only adds batches that are
+// thrown away (15.2 us with three more, 12.7 so).
 constexpr int kPlainUnroll = 8;  // matrix instructions (2 of the contraction each) per batch of loads
-template <int NW>
+template <int NW, bool SUMS>
 __device__ __forceinline__ void plain_product(const float *A, int lda, const float *X, const float *mass, float *out,
                                               int ldx, int kd, int M, int N, int32_t *bad, float *lds, int wg,
                                               int nwg) {
@@ -192,7 +201,7 @@ __device__ __forceinline__ void plain_product(const float *A, int lda, const flo
                 float v = 0.f;
                 if (mm > 0.f) {
                     if (!(s >= kPlainLo && s <= kPlainHi)) bad[n] = 1;
-                    v = mm * __builtin_amdgcn_rcpf(s);
+                    v = SUMS ? s : mm * __builtin_amdgcn_rcpf(s);
                 }
                 out[at] = v;
             }
@@ -203,12 +212,12 @@ __device__ __forceinline__ void plain_product(const float *A, int lda, const flo
 template <int NW>
 __device__ __forceinline__ void plain_u(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, P.bad, lds, wg, nwg);
+    plain_product<NW, false>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, P.bad, lds, wg, nwg);
 }
 template <int NW>
 __device__ __forceinline__ void plain_v(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, P.bad, lds, wg, nwg);
+    plain_product<NW, false>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, P.bad, lds, wg, nwg);
 }
 // The first v-update.
 __global__ __launch_bounds__(512) void sk_plain_first(TiledArgs T) {
@@ -216,16 +225,37 @@ __global__ __launch_bounds__(512) void sk_plain_first(TiledArgs T) {
     if (!plain_taken(T)) return;
     plain_v<8>(T, lds, (int)blockIdx.x, (int)gridDim.x);
 }
+// The sums of the last u-update (8 wavefronts, as the sweeps) or v-update (4, as
+// the merges) again, in the masses' place: the last sweep runs no product, so
+// Ut still is what the last v-update took.  (Kept out of the two launches of an
+// iteration: a test for the last one there moved the sweep's code, 1.2 % on a
+// cost out of range.)
+template <int NW, bool ROWS>
+__global__ __launch_bounds__(64 * NW) void sk_plain_last(TiledArgs T) {
+    extern __shared__ float lds[];
+    if (!plain_taken(T)) return;
+    const PlainArgs &P = T.plain;
+    if (ROWS)
+        plain_product<NW, true>(P.Kt, P.l1, P.Vt, P.mut, P.mut, P.lb, P.p2, T.d1, T.B, P.bad, lds, (int)blockIdx.x,
+                                (int)gridDim.x);
+    else
+        plain_product<NW, true>(P.K, P.l2, P.Ut, P.nut, P.nut, P.lb, P.p1, T.d2, T.B, P.bad, lds, (int)blockIdx.x,
+                                (int)gridDim.x);
+}
 
-// log2 v (-inf at 0) to half a unit in the last place: the hardware's logarithm
-// of the mantissa alone, added to the exponent (of the whole number it is off
-// by a unit of the result, 2e-6 at 2^-20).
-__device__ __forceinline__ float exact_lg2(float v) {
-    return (float)__builtin_amdgcn_frexp_expf(v) + lg2(__builtin_amdgcn_frexp_mantf(v));
+// log2(mass / sum), -inf without mass, to half a unit in the last place: the
+// hardware's logarithm of a mantissa alone, added to the exponent (of the whole
+// number it is off by a unit of the result, 2e-6 at 2^-20).
+__device__ __forceinline__ float plain_potential(float mass, float sum) {
+    if (!(mass > 0.f)) return neg_inf();
+    const float q = __builtin_amdgcn_frexp_mantf(mass) * __builtin_amdgcn_rcpf(__builtin_amdgcn_frexp_mantf(sum));
+    const int e = __builtin_amdgcn_frexp_expf(mass) - __builtin_amdgcn_frexp_expf(sum) + __builtin_amdgcn_frexp_expf(q);
+    return (float)e + lg2(__builtin_amdgcn_frexp_mantf(q));
 }
 
 // Back to the sweeps' potentials for the closing statistics: a = log2 u,
-// b = log2 v + s min C, the state of a problem that ran all its iterations.
+// b = log2 v + s min C from the last sums, the state of a problem that ran all
+// its iterations.
 // A problem out of range is solved here from its start in the log domain, one
 // work-group for all its iterations.
 constexpr int kRedoThreads = 1024;
@@ -235,19 +265,15 @@ __global__ __launch_bounds__(kRedoThreads) void sk_plain_finish(TiledArgs T) {
     const int b = blockIdx.x, d1 = T.d1, d2 = T.d2, n = T.n_iter;
     float *a = T.a + (size_t)b * d1, *bn = T.bbuf + (size_t)(n & 1) * T.B * T.d2p + (size_t)b * T.d2p;
     if (threadIdx.x == 0) T.state[b] = 0;
+    const float *mu = T.mu + (size_t)b * d1, *nu = T.nu + (size_t)b * d2;
     if (P.bad[b] == 0) {
         const float shift = T.s * unordered(P.range[0]);
-        for (int i = threadIdx.x; i < d1; i += kRedoThreads) {
-            const float u = P.Ut[(size_t)i * P.lb + b];
-            a[i] = exact_lg2(u);
-        }
-        for (int j = threadIdx.x; j < d2; j += kRedoThreads) {
-            const float v = P.Vt[(size_t)j * P.lb + b];
-            bn[j] = exact_lg2(v) + shift;
-        }
+        for (int i = threadIdx.x; i < d1; i += kRedoThreads)
+            a[i] = plain_potential(mu[i], P.mut[(size_t)i * P.lb + b]);
+        for (int j = threadIdx.x; j < d2; j += kRedoThreads)
+            bn[j] = plain_potential(nu[j], P.nut[(size_t)j * P.lb + b]) + shift;
         return;
     }
-    const float *mu = T.mu + (size_t)b * d1, *nu = T.nu + (size_t)b * d2;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int k = 1; k <= n; ++k) {
         for (int j = threadIdx.x; j < d2; j += kRedoThreads) {

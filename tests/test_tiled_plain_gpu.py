@@ -9,7 +9,7 @@ import torch
 import oracle
 import paper_1907_01729_amd as sk
 import workloads
-from parity_util import gauge_fixed_errors, loss_rel_err
+from parity_util import GRAD_RTOL, gauge_fixed_errors, loss_rel_err, rel_err_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +62,26 @@ def test_problem_out_of_range():
     one = oracle.forward(mu[7:8], nu[7:8], p.C, p.lam, 120)
     ea, eb = gauge_fixed_errors(mu[7:8], nu[7:8], out["alpha"][7:8], out["beta"][7:8], one["alpha"], one["beta"])
     assert max(ea, eb) <= 1e-3 and loss_rel_err(out["loss"][7:8], one["loss"]) <= 1e-4
+
+
+def test_small_masses():
+    """Masses down to fp32's smallest subnormal: a scaling may underflow, the potentials of the returned iterate may
+    not, and the gradient of the sample (centred over the support) stays finite."""
+    p = workloads.random_problem(44, 224, 640, 640, 0.05, 120)
+    tiny = np.array([1e-30, 1e-38, 1e-43, 1.5e-45], np.float32)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    mu[5, [3, 99, 400, 639]] = tiny
+    nu[6, [3, 99, 400, 639]] = tiny
+    mu[7, 100:104] = nu[7, 300:304] = tiny
+    z = 15.0 * np.random.default_rng(45).standard_normal((2, 640))  # confident classifiers
+    mu[9], nu[9] = (np.exp(z - z.max(1, keepdims=True)) / np.exp(z - z.max(1, keepdims=True)).sum(1, keepdims=True))
+    sample = [4, 5, 6, 7, 9]
+    assert (mu[9] < 1e-37).any() and (nu[9] < 1e-37).any()
+    out, ref, el, ep = run(mu, nu, p.C, p.lam, 120, sample)  # finite on the supports
+    # masses below 2^-126 have as few as one significant bit, the same for the oracle: the bounds stand
+    assert el <= LOSS and ep <= 10 * POT, (el, ep)
+    g = sk.sinkhorn_backward(torch.ones(224, device="cuda:0"), _t(mu), _t(nu), _t(p.C), p.lam, _t(out["alpha"]),
+                             _t(out["beta"]))
+    r = oracle.backward(np.ones(len(sample)), mu[sample], nu[sample], p.C, p.lam, ref["alpha"], ref["beta"])
+    for k in ("grad_mu", "grad_nu"):
+        assert rel_err_rows(g[k].cpu().numpy()[sample], r[k]) <= GRAD_RTOL
