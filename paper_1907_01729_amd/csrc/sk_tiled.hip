@@ -54,13 +54,15 @@ constexpr float kPlainLo = 8.2718061255302767e-25f, kPlainHi = 1.267650600228229
 constexpr float kPlainSpan = 64.f;
 
 // Device state: range[0], range[1] = order-preserving integers of the cost's
-// smallest and largest entry, range[2] = 1 when the plain form is taken.
+// smallest and largest entry, range[2] = 1 when the plain form is taken,
+// range[3] != 0 when an entry is not finite.
 struct PlainArgs {
     int32_t *range;   // null: not asked
     float *K, *Kt;    // [p1][p2], [p2][p1], rows of l2 and l1 floats
     float *Ut, *Vt;   // [p1][pb], [p2][pb], rows of lb floats
     float *mut, *nut;  // the masses in the same order; at the end, the last sums
     int32_t *bad;     // [B] problems to solve again
+    float *factor;    // [B][2] factors of mu and nu
     int p1, p2, pb;   // padded d1, d2, B
     int l1, l2, lb;   // their row strides
 };
@@ -645,6 +647,114 @@ __global__ __launch_bounds__(kThreads) void sk_tiled_sweep(TiledArgs T, int k) {
         T.rowerr[((size_t)plane * T.R + r) * T.B + b] = re;
         if (STATS) T.lossp[(size_t)r * T.B + b] = lo;
     }
+}
+
+// ---- Closing the plain form (sk_tiled_plain.h) ----
+//
+// Back to the sweeps' potentials for the closing statistics: a = log2 u,
+// b = log2 v + s min C from the last sums, the state of a problem that ran all
+// its iterations.
+//
+// A problem out of range is solved here from its start in the log domain, one
+// work-group for all its iterations, as the sweep and the merge do them: one
+// exponential per cell, rows in turn over the wavefronts, column sums in
+// registers.  Bound by the arithmetic of one CU (the sweeps give each of 256
+// problems one CU too).  A problem of 1000 x 1000 adds 9 ms to 100 iterations of
+// its batch (18 without the loads a row ahead, 33 with a thread per column
+// running down the rows; the whole batch in the sweeps: 6.9).
+template <int NCW>
+constexpr int kRedoWaves = NCW <= 16 ? 16 : NCW <= 32 ? 8 : 4;  // four or five registers per column
+// A row of the cost already in registers (columns past d2 hold any value).
+template <int NCW>
+struct RegCost {
+    const float (&raw)[NCW];
+    int lane, d2;
+    float s;
+    __device__ __forceinline__ float operator()(int c) const { return lane + 64 * c < d2 ? -s * raw[c] : kPadCost; }
+};
+template <int NCW>
+__global__ __launch_bounds__(64 * kRedoWaves<NCW>) void sk_plain_finish(TiledArgs T) {
+    constexpr int NW = kRedoWaves<NCW>, NT = 64 * NW;
+    extern __shared__ float lds[];  // [NW][NCW * 64] column partials
+    if (!plain_taken(T)) return;
+    const PlainArgs &P = T.plain;
+    const int b = blockIdx.x, d1 = T.d1, d2 = T.d2;
+    const float *mu = T.mu + (size_t)b * d1, *nu = T.nu + (size_t)b * d2;
+    float *a = T.a + (size_t)b * d1, *bp = T.bbuf + (size_t)b * T.d2p;
+    const size_t plane = (size_t)T.B * T.d2p;
+    if (threadIdx.x == 0) T.state[b] = 0;
+    if (P.bad[b] == 0) {
+        float *bn = bp + (T.n_iter & 1) * plane;
+        // log2 u_k = log2 mu - log2 sum + k log2 f2 - (k - 1) log2 f1, log2 v_k = log2 nu - log2 sum + (k - 1) log2(f1 / f2)
+        const double l1 = log2((double)P.factor[2 * b]), l2 = log2((double)P.factor[2 * b + 1]), k1 = T.n_iter - 1;
+        const float su = (float)(l2 + k1 * (l2 - l1)), sv = (float)((double)(T.s * unordered(P.range[0])) + k1 * (l1 - l2));
+        for (int i = threadIdx.x; i < d1; i += NT) a[i] = plain_potential(mu[i], P.mut[(size_t)i * P.lb + b]) + su;
+        for (int j = threadIdx.x; j < d2; j += NT) bn[j] = plain_potential(nu[j], P.nut[(size_t)j * P.lb + b]) + sv;
+        return;
+    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    bool some1 = false, some2 = false;
+    for (int i = threadIdx.x; i < d1; i += NT) some1 = some1 || mu[i] > 0.f;
+    for (int j = threadIdx.x; j < d2; j += NT) some2 = some2 || nu[j] > 0.f;
+    some1 = __syncthreads_or(some1);
+    some2 = __syncthreads_or(some2);
+    // Without mass on one side the first iteration's potentials are infinite
+    // and every later one gives them again.
+    const int n = some1 && some2 ? T.n_iter : 1;
+    for (int j = threadIdx.x; j < d2; j += NT)
+        bp[plane + j] = nu[j] > 0.f ? log2f(nu[j]) - col_lse_exact(T, b, j) : neg_inf();
+    __threadfence_block();
+    __syncthreads();
+    for (int k = 1; k <= n; ++k) {
+        const float *bsrc = bp + (k & 1) * plane;
+        float bv[NCW], colpart[NCW], rowerr = 0.f, losspart = 0.f;
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) {
+            bv[c] = bsrc[lane + 64 * c];  // 0 past d2 (padded stride)
+            colpart[c] = 0.f;
+        }
+        // The next row is loaded over this row's work (past the last: clamped)
+        // where the registers hold it.
+        constexpr bool AHEAD = NCW <= 32;
+        float next[NCW], anext, munext;
+        auto load_row = [&](int i) {
+            const int ii = min(i, d1 - 1);
+            anext = a[ii];
+            munext = mu[ii];
+            const float *row = T.C + (size_t)ii * d2;
+#pragma unroll
+            for (int c = 0; c < NCW; ++c) next[c] = row[min(lane + 64 * c, d2 - 1)];
+        };
+        if (AHEAD) load_row(w);
+        for (int i = w; i < d1; i += NW) {
+            if (!AHEAD) load_row(i);
+            float raw[NCW];
+#pragma unroll
+            for (int c = 0; c < NCW; ++c) raw[c] = next[c];
+            const float ai = anext, mui = munext;
+            if (AHEAD) load_row(i + NW);
+            row_step<NCW, false>(RegCost<NCW>{raw, lane, d2, T.s}, ai, mui, a + i, bv, colpart, rowerr, losspart, lane);
+        }
+        if (k == n) break;
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) lds[w * NCW * 64 + 64 * c + lane] = colpart[c];
+        __threadfence_block();
+        __syncthreads();
+        float *bnew = bp + ((k + 1) & 1) * plane;
+        for (int j = threadIdx.x; j < d2; j += NT) {
+            float cs = 0.f;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) cs += lds[q * NCW * 64 + j];
+            float v = neg_inf();
+            if (nu[j] > 0.f)
+                v = cs >= kSumLo && cs <= kSumHi ? bsrc[j] + log2f(nu[j]) - lg2(cs) : log2f(nu[j]) - col_lse_exact(T, b, j);
+            bnew[j] = v;
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
+    if ((n ^ T.n_iter) & 1)
+        for (int j = threadIdx.x; j < d2; j += NT) bp[(T.n_iter & 1) * plane + j] = bp[(n & 1) * plane + j];
 }
 
 // ---- Rows wider than one wavefront's registers hold (d2 > kTiledMaxD2) ----
@@ -1900,7 +2010,7 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             if (e != hipSuccess) return e;
         }
         if (T.plain.range) {
-            hipLaunchKernelGGL(sk_plain_range, dim3(128), dim3(256), 0, st, T);
+            hipLaunchKernelGGL(sk_plain_range, dim3(kPlainRangeGroups + T.B), dim3(256), 0, st, T);
             hipLaunchKernelGGL(sk_plain_setup, dim3(512), dim3(256), 0, st, T);
         }
         launch_col_exact(T, st);
@@ -1911,11 +2021,6 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             sweep(k);
             if (k < T.n_iter) launch_merge(T, k, st);
         }
-    }
-    if (T.plain.range) {
-        hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
-        hipLaunchKernelGGL((sk_plain_last<4, false>), dim3(512), dim3(256), sizeof(float) * 1024 * 4, st, T);
-        hipLaunchKernelGGL(sk_plain_finish, dim3(T.B), dim3(kRedoThreads), 0, st, T);
     }
     stats();
     launch_final(T, st);
@@ -1975,10 +2080,13 @@ hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
     hipError_t e = allow_lds(stats_kernel, lds);
     if (e != hipSuccess) return e;
     // The last sweep beside the plain form runs no product (see sk_plain_last).
+    constexpr size_t finish_lds = sizeof(float) * kRedoWaves<NCW> * NCW * 64;
+    auto finish = &sk_plain_finish<NCW>;
     auto sweep = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, false>;
     auto both = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>;
     e = allow_lds(sweep, lds);
     if (e == hipSuccess && T.plain.range) e = allow_lds(both, lds);
+    if (e == hipSuccess && T.plain.range) e = allow_lds(finish, finish_lds);
     if (e != hipSuccess) return e;
     return run_sequence(
         T, st,
@@ -1988,7 +2096,14 @@ hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
             else
                 hipLaunchKernelGGL(*sweep, grid, blk, lds, st, T, k);
         },
-        [&]() { hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0); });
+        [&]() {
+            if (T.plain.range) {
+                hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
+                hipLaunchKernelGGL((sk_plain_last<4, false>), dim3(512), dim3(256), sizeof(float) * 1024 * 4, st, T);
+                hipLaunchKernelGGL(*finish, dim3(T.B), dim3(64 * kRedoWaves<NCW>), finish_lds, st, T);
+            }
+            hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0);
+        });
 }
 
 template <int NCW, int D>
@@ -2170,7 +2285,7 @@ bool plain_wanted(const FwdArgs &a, int W, size_t floats, PlainArgs *P) {
     P->l1 = stride(P->p1);
     P->l2 = stride(P->p2);
     P->lb = stride(P->pb);
-    const size_t need = (size_t)P->p1 * P->l2 + (size_t)P->p2 * P->l1 + 2 * (size_t)(P->p1 + P->p2) * P->lb + a.B;
+    const size_t need = (size_t)P->p1 * P->l2 + (size_t)P->p2 * P->l1 + 2 * (size_t)(P->p1 + P->p2) * P->lb + 3 * (size_t)a.B;
     return need <= floats;
 }
 
@@ -2230,7 +2345,8 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
         P.Vt = P.Ut + (size_t)P.p1 * P.lb;
         P.mut = P.Vt + (size_t)P.p2 * P.lb;
         P.nut = P.mut + (size_t)P.p1 * P.lb;
-        P.bad = reinterpret_cast<int32_t *>(P.nut + (size_t)P.p2 * P.lb);
+        P.factor = P.nut + (size_t)P.p2 * P.lb;
+        P.bad = reinterpret_cast<int32_t *>(P.factor + 2 * (size_t)a.B);
     }
     if (W == 8) return vec4 ? dispatch_shared<8, true>(T, ncw, st) : dispatch_shared<8, false>(T, ncw, st);
     if (W == 4) return vec4 ? dispatch_shared<4, true>(T, ncw, st) : dispatch_shared<4, false>(T, ncw, st);

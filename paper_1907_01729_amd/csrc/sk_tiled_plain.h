@@ -6,9 +6,15 @@
 // matrix product of K with all the batch's scalings.  It is taken where the
 // scaled cost spans at most 64 bits (as in the resident kernels).  Every sum is
 // then within [2^-64, 1] of the sum of its operand's scalings, whose product
-// stays within [1, 2^64]; a sum that leaves [2^-80, 2^100] all the same (it
-// takes masses far from a histogram) marks its problem, which is solved again
-// in the log domain.
+// stays within [1, 2^64]; a sum that leaves [2^-80, 2^100] all the same (no mass
+// on one side, or masses that are not finite) marks its problem, which is
+// solved again in the log domain (sk_plain_finish).
+//
+// Masses that do not sum to one would move the scalings by the ratio of their
+// sums in every iteration.  They are divided by their sums first; with masses
+// f1 mu and f2 nu in the place of mu and nu the iteration gives u_k (f1/f2)^k
+// and v_k f2 (f2/f1)^(k-1), which the returned potentials take back.  (Sums
+// that move nothing by more than 8 bits in all are left as they are.)
 //
 // Scalings are not guarded (the resident kernels guard both): a small mass may
 // give one below 2^-126, where it has few bits or none.  As an operand that
@@ -42,12 +48,29 @@ __device__ __forceinline__ int32_t ordered(float x) {
 }
 __device__ __forceinline__ float unordered(int32_t i) { return __int_as_float(i >= 0 ? i : i ^ 0x7fffffff); }
 
-// Smallest and largest entry of the cost (a NaN fails the test in plain_taken
-// through range[3]).
+// Work-groups below kPlainRangeGroups: smallest and largest entry of the cost
+// (one that is not finite fails the test in plain_fits through range[3]).  The
+// others, one per problem: the factors f1, f2 of its masses.
+constexpr int kPlainRangeGroups = 128;
 __global__ __launch_bounds__(256) void sk_plain_range(TiledArgs T) {
     if (splits(T)) return;
     __shared__ float least[4], most[4];
-    const size_t n = (size_t)T.d1 * T.d2, step = (size_t)gridDim.x * 256;
+    if (blockIdx.x >= kPlainRangeGroups) {
+        const int b = (int)blockIdx.x - kPlainRangeGroups;
+        float m1 = 0.f, m2 = 0.f;
+        for (int i = threadIdx.x; i < T.d1; i += 256) m1 += fmaxf(T.mu[(size_t)b * T.d1 + i], 0.f);
+        for (int j = threadIdx.x; j < T.d2; j += 256) m2 += fmaxf(T.nu[(size_t)b * T.d2 + j], 0.f);
+        m1 = block_sum_n<256>(m1, least);
+        m2 = block_sum_n<256>(m2, most);
+        if (threadIdx.x != 0) return;
+        const float l1 = log2f(m1), l2 = log2f(m2), f1 = 1.f / m1, f2 = 1.f / m2;
+        const bool far = fabsf(l1 - l2) * (float)T.n_iter + fabsf(l1) + fabsf(l2) > 8.f;  // (NaN: not)
+        const bool usable = f1 > 0.f && f2 > 0.f && f1 < __builtin_inff() && f2 < __builtin_inff();
+        T.plain.factor[2 * b] = far && usable ? f1 : 1.f;
+        T.plain.factor[2 * b + 1] = far && usable ? f2 : 1.f;
+        return;
+    }
+    const size_t n = (size_t)T.d1 * T.d2, step = (size_t)kPlainRangeGroups * 256;
     float lo = __builtin_inff(), hi = -__builtin_inff();
     bool bad = false;
     for (size_t u = (size_t)blockIdx.x * 256 + threadIdx.x; u < n; u += 8 * step) {
@@ -108,6 +131,7 @@ __global__ __launch_bounds__(256) void sk_plain_setup(TiledArgs T) {
             float x = 0.f;
             if (r < rows && c < cols) {
                 x = src[(size_t)r * cols + c];
+                if (!cost) x *= P.factor[2 * r + (first ? 0 : 1)];
                 if (cost) {  // 2^(-s (C - lo)), the integer part of the exponent kept apart
                     const double e = -(double)T.s * ((double)x - (double)lo), f = floor(e);
                     x = ldexpf(exp2f((float)(e - f)), (int)f);
@@ -143,7 +167,7 @@ __device__ __forceinline__ bool plain_taken(const TiledArgs &T) { return T.plain
 // out[m][n] = mass[m][n] / sum_k A[k][m] X[k][n] over m < M, n < N in tiles of
 // 32 x 32: work-groups wg, wg + nwg, ... of NW wavefronts; lds: NW * 1024
 // floats.  kd is a multiple of 32; out's rows and columns past its size keep
-// 0.  SUMS: out takes the sums (of positive masses) themselves.  One batch of
+// 0.  SUMS: out takes the sums themselves.  One batch of
 // loads is in flight beside a batch's products: bound by those loads (20 cycles
 // per 256 bytes and CU), so loading further ahead only adds batches that are
 // thrown away (15.2 us with three more, 12.7 so).
@@ -198,10 +222,10 @@ __device__ __forceinline__ void plain_product(const float *A, int lda, const flo
             if (m < M && n < N) {
                 const size_t at = (size_t)m * ldx + n;
                 const float mm = mass[at];
-                float v = 0.f;
+                float v = SUMS ? s : 0.f;
                 if (mm > 0.f) {
                     if (!(s >= kPlainLo && s <= kPlainHi)) bad[n] = 1;
-                    v = SUMS ? s : mm * __builtin_amdgcn_rcpf(s);
+                    if (!SUMS) v = mm * __builtin_amdgcn_rcpf(s);
                 }
                 out[at] = v;
             }
@@ -251,55 +275,4 @@ __device__ __forceinline__ float plain_potential(float mass, float sum) {
     const float q = __builtin_amdgcn_frexp_mantf(mass) * __builtin_amdgcn_rcpf(__builtin_amdgcn_frexp_mantf(sum));
     const int e = __builtin_amdgcn_frexp_expf(mass) - __builtin_amdgcn_frexp_expf(sum) + __builtin_amdgcn_frexp_expf(q);
     return (float)e + lg2(__builtin_amdgcn_frexp_mantf(q));
-}
-
-// Back to the sweeps' potentials for the closing statistics: a = log2 u,
-// b = log2 v + s min C from the last sums, the state of a problem that ran all
-// its iterations.
-// A problem out of range is solved here from its start in the log domain, one
-// work-group for all its iterations.
-constexpr int kRedoThreads = 1024;
-__global__ __launch_bounds__(kRedoThreads) void sk_plain_finish(TiledArgs T) {
-    if (!plain_taken(T)) return;
-    const PlainArgs &P = T.plain;
-    const int b = blockIdx.x, d1 = T.d1, d2 = T.d2, n = T.n_iter;
-    float *a = T.a + (size_t)b * d1, *bn = T.bbuf + (size_t)(n & 1) * T.B * T.d2p + (size_t)b * T.d2p;
-    if (threadIdx.x == 0) T.state[b] = 0;
-    const float *mu = T.mu + (size_t)b * d1, *nu = T.nu + (size_t)b * d2;
-    if (P.bad[b] == 0) {
-        const float shift = T.s * unordered(P.range[0]);
-        for (int i = threadIdx.x; i < d1; i += kRedoThreads)
-            a[i] = plain_potential(mu[i], P.mut[(size_t)i * P.lb + b]);
-        for (int j = threadIdx.x; j < d2; j += kRedoThreads)
-            bn[j] = plain_potential(nu[j], P.nut[(size_t)j * P.lb + b]) + shift;
-        return;
-    }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int k = 1; k <= n; ++k) {
-        for (int j = threadIdx.x; j < d2; j += kRedoThreads) {
-            float m = kNegBig, s = 0.f;
-            for (int i = 0; i < d1; ++i) {
-                const float x = a[i] - T.s * T.C[(size_t)i * d2 + j], mn = fmaxf(m, x);
-                s = s * ex2(m - mn) + ex2(x - mn);
-                m = mn;
-            }
-            bn[j] = nu[j] > 0.f ? log2f(nu[j]) - (m + lg2(s)) : neg_inf();
-        }
-        __threadfence_block();
-        __syncthreads();
-        for (int i = w; i < d1; i += kRedoThreads / 64) {
-            if (!(mu[i] > 0.f)) continue;
-            float m = kNegBig, s = 0.f;
-            for (int j = lane; j < d2; j += 64) {
-                const float x = bn[j] - T.s * T.C[(size_t)i * d2 + j], mn = fmaxf(m, x);
-                s = s * ex2(m - mn) + ex2(x - mn);
-                m = mn;
-            }
-            const float top = wave_max(m);
-            s = wave_sum(s * ex2(m - top));
-            if (lane == 0) a[i] = log2f(mu[i]) - (top + lg2(s));
-        }
-        __threadfence_block();
-        __syncthreads();
-    }
 }

@@ -2,6 +2,8 @@
 most 64 bits, products on the matrix cores): sizes around the 32 x 32 tiles,
 zero masses, a cost just outside the range (the sweeps), and a problem whose
 sums leave fp32's guarded range (solved again in the log domain)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -9,7 +11,7 @@ import torch
 import oracle
 import paper_1907_01729_amd as sk
 import workloads
-from parity_util import GRAD_RTOL, gauge_fixed_errors, loss_rel_err, rel_err_rows
+from parity_util import GRAD_RTOL, LOSS_RTOL, POT_ATOL, gauge_fixed_errors, loss_rel_err, rel_err_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -55,8 +57,8 @@ def test_cost_out_of_range():
 def test_problem_out_of_range():
     p = workloads.random_problem(43, 224, 640, 640, 0.05, 120)
     mu, nu = p.mu.copy(), p.nu.copy()
-    mu[7] *= np.float32(2.0 ** 104)  # not a histogram: the sums pass 2^100
-    nu[7] *= np.float32(2.0 ** 104)
+    mu[7] *= np.float32(2.0 ** 112)  # not a histogram: as they are, these masses make sums of 2^103
+    nu[7] *= np.float32(2.0 ** 112)
     out, ref, el, ep = run(mu, nu, p.C, p.lam, 120, [0, 6, 8, 223])
     assert el <= LOSS and ep <= POT
     one = oracle.forward(mu[7:8], nu[7:8], p.C, p.lam, 120)
@@ -85,3 +87,81 @@ def test_small_masses():
     r = oracle.backward(np.ones(len(sample)), mu[sample], nu[sample], p.C, p.lam, ref["alpha"], ref["beta"])
     for k in ("grad_mu", "grad_nu"):
         assert rel_err_rows(g[k].cpu().numpy()[sample], r[k]) <= GRAD_RTOL
+
+
+def test_masses_that_do_not_sum_to_one():
+    """Masses of 64, 1 / 5 or 1.01 against 1 move the scalings by their ratio in every iteration, the first two out of
+    fp32; as in the log domain, the potentials follow."""
+    p = workloads.random_problem(49, 224, 640, 640, 0.05, 120, zero_frac=0.1)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    mu[5] *= np.float32(64.0)
+    mu[6] *= np.float32(0.2)
+    mu[7] *= np.float32(1.01)
+    nu[8] *= np.float32(1e-20)
+    _, ref, el, ep = run(mu, nu, p.C, p.lam, 120, [4, 5, 6, 7, 8])
+    # potentials of 120 log 64 = 500 and 119 log 1e20 = 5480, rounded to fp32 (2^-25 of them) and from base 2, and the
+    # exponents of the plan with them
+    top = 5500.0
+    assert ep <= 2.0 ** -23 * top and el <= 2.0 ** -22 * top
+
+
+@pytest.mark.parametrize("B, d1, d2", [(1024, 500, 400), (768, 400, 1000), (384, 500, 1030), (384, 300, 2100)])
+def test_problem_solved_again(B, d1, d2):
+    """The log-domain solve of a problem out of range, here by masses whose sum fp32 does not hold, at each of its
+    column widths."""
+    p = workloads.random_problem(46, B, d1, d2, 0.05, 60, zero_frac=0.1)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    mu[7, :3] = nu[7, :3] = 1.2e38
+    out, _, el, _ = run(mu, nu, p.C, p.lam, 60, [6])
+    assert el <= LOSS
+    one = oracle.forward(mu[7:8], nu[7:8], p.C, p.lam, 60)
+    ea, eb = gauge_fixed_errors(mu[7:8], nu[7:8], out["alpha"][7:8], out["beta"][7:8], one["alpha"], one["beta"])
+    assert max(ea, eb) <= POT_ATOL
+
+
+def test_problem_without_mass():
+    """Padded samples (no mass on one side, or on both) leave the other problems alone; without a row mass they come
+    back as the sweeps give them."""
+    p = workloads.random_problem(47, 224, 640, 640, 0.05, 120)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    mu[7] = 0.0
+    mu[8] = nu[8] = 0.0
+    nu[9] = 0.0
+    whole, out = ({k: v.cpu().numpy() for k, v in sk.sinkhorn_forward(_t(m), _t(n), _t(p.C), p.lam, 120).items()}
+                  for m, n in ((p.mu, p.nu), (mu, nu)))
+    log = {k: v.cpu().numpy() for k, v in
+           sk.sinkhorn_forward_select("log", _t(mu), _t(nu), _t(p.C), p.lam, 120).items()}
+    rest = [b for b in range(224) if b not in (7, 8, 9)]
+    for k in out:
+        np.testing.assert_array_equal(out[k][7:9], log[k][7:9], err_msg=k)
+        np.testing.assert_array_equal(out[k][rest], whole[k][rest], err_msg=k)
+    assert np.isneginf(out["alpha"][7]).all() and np.isneginf(out["beta"][8]).all() and out["loss"][8] == 0.0
+
+
+@pytest.mark.parametrize("what", ["no mass", "sum 64", "sum above fp32"])
+def test_time_with_a_problem_out_of_range(what):
+    """A batch with such a problem costs no more than it does in the log-domain sweeps."""
+    p = workloads.random_problem(48, 256, 1000, 1000, 0.05, 100)
+    mu, nu = p.mu.copy(), p.nu.copy()
+    if what == "no mass":
+        mu[7] = 0.0
+    elif what == "sum 64":
+        mu[7] *= np.float32(64.0)
+    else:
+        mu[7, :3] = nu[7, :3] = 1.2e38
+    m, n, C = _t(mu), _t(nu), _t(p.C)
+
+    def best(f):
+        ts = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            ts.append(time.perf_counter() - t)
+        return min(ts)
+
+    sweeps = best(lambda: sk.sinkhorn_forward_select("log", m, n, C, 0.05, 100))
+    plain = best(lambda: sk.sinkhorn_forward(m, n, C, 0.05, 100))
+    print(f"{what}: {1e3 * plain:.2f} ms, in the sweeps {1e3 * sweeps:.2f} ms", flush=True)
+    assert plain <= 1.1 * sweeps
