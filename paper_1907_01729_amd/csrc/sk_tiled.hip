@@ -1906,8 +1906,13 @@ int padded_width(int d2, int kind) {
     return w;
 }
 
-// Row blocks above which the merge splits them too (sk_tiled_merge_rows).
-bool merge_by_rows(int R) { return R >= 32; }
+// The merge splits the row blocks too (sk_tiled_merge_rows) from 32 of them,
+// while a problem has at most 1024 slices of 64 columns: the slices' errors are
+// added in fixed point at 2^(45 - log2 slices) units per unit of error (see
+// take_stop), at 1024 slices within 512 of 2^35 units, 1.5e-8; of 16384 slices
+// (2^20 columns) a sum of up to 4e-6 could read as 0, and 32768 no longer fit
+// the count's 15 bits.  (Slices of 1024 columns are 16384 at most.)
+bool merge_by_rows(int R, int d2) { return R >= 32 && d2 <= 64 * 1024; }
 // Work-groups per problem of the merge after a sweep (4 columns per thread).
 int merge_slices(int d2) { return (d2 + 4 * kMergeColsThreads - 1) / (4 * kMergeColsThreads); }
 
@@ -2205,7 +2210,7 @@ TiledArgs tiled_args(const FwdArgs &a, int kind, void *ws, Layout *Lout) {
     T.sep_mode = nullptr;
     T.sep = nullptr;
     T.plain = PlainArgs{};
-    T.merge_rows = merge_by_rows(R);
+    T.merge_rows = merge_by_rows(R, a.d2);
     T.MS = T.merge_rows ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     // A merge in slices has its accumulators in their own region, else in the
     // loss partials' (8 bytes per problem of at least 4 R; they are written
@@ -2402,10 +2407,10 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
         snprintf(sweep, sizeof sweep, "sk_tiled_sweep<%d> (one problem per work-group)", ncw);
     }
     char mrg[128];
-    const int slices = merge_by_rows(R) ? (a.d2 + 63) / 64 : merge_slices(a.d2);
+    const int slices = merge_by_rows(R, a.d2) ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     if (merge)
         snprintf(mrg, sizeof mrg, "%s<%d> after each sweep (%d work-group%s per problem)",
-                 merge_by_rows(R) ? "sk_tiled_merge_rows" : "sk_tiled_merge_cols", kMergeColsThreads, slices,
+                 merge_by_rows(R, a.d2) ? "sk_tiled_merge_rows" : "sk_tiled_merge_cols", kMergeColsThreads, slices,
                  slices == 1 ? "" : "s");
     else
         snprintf(mrg, sizeof mrg, "the merge folded into the next sweep");

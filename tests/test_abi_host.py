@@ -175,6 +175,15 @@ def test_few_wide_problems_fit_the_library_scratch(B, d1):
     assert sk.sinkhorn_workspace_bytes(B, d1, 4096, 0, 0.1, 10) <= sk.NOALLOC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("d2, merge", [(65536, "rows"), (65537, "cols"), (2097152, "cols"), (1 << 24, "cols")])
+def test_merge_slices_of_the_widest_rows(d2, merge):
+    # The early stop counts a problem's slices in 15 bits, and they are a grid dimension: at most 16384 (the widest
+    # rows, 1024 columns each).
+    line = sk.sinkhorn_describe(1, 128, d2, 0, 0.1, 10, 1e-3)
+    m = re.search(r"sk_tiled_merge_(\w+)<256> after each sweep \((\d+) work-group", line)
+    assert m and m.group(1) == merge and int(m.group(2)) <= 16384, line
+
+
 def test_points_workspace_sizes():
     # on-the-fly sweep (per-sample clouds, tiled shape, D <= 3, d2 <= 2048): no cost matrix in the workspace
     on_the_fly = sk.sinkhorn_points_workspace_bytes(32, 1024, 2048, 1, 3, 0.05, 100)
