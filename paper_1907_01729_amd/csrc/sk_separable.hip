@@ -425,8 +425,8 @@ __device__ __forceinline__ float sep_v(const SepState &S, int w, int what, const
         const Scaled x = get(S.plane + at);
         const Scaled v = update(in2 ? nuj : 0.f, line_sum<PO, BS>(S.E[kTabV1], S.Lr[kTabV1], S.yb, lane, in1 ? x : none()));
         if (what != kVPlain) {
-            if (what >= kVKeepErr && in2 && nuj > 0.f)
-                err += fabsf(__builtin_fmaf(nuj, ratio(get(old + r * S.vld + o), v), -nuj));
+            if (what >= kVKeepErr && in2)  // a column without mass is empty: its error is |nu|, NaN where nu is
+                err += nuj > 0.f ? fabsf(__builtin_fmaf(nuj, ratio(get(old + r * S.vld + o), v), -nuj)) : fabsf(nuj);
             if (what == kVErr) continue;
             if (in2) {
                 put(keep + r * S.vld + o, v);

@@ -141,3 +141,23 @@ def test_cost_left_to_the_sweeps(case):
     out = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, 170)
     ref = oracle.forward(mu, nu, C[None], lam, 170)
     assert loss_rel_err(out["loss"].cpu().numpy(), ref["loss"]) <= 1e-4
+
+
+@pytest.mark.parametrize("value", [np.nan, -0.25])
+def test_split_bad_mass_reaches_the_marginal_error(value):
+    """A NaN in nu makes the sample's marginal error NaN, a negative mass counts as missed (as in the sweeps); neither
+    lets the sample stop."""
+    mu, nu, C = make(22, 4, (18, 17), (18, 17), "sq")
+    bad = nu.copy()
+    bad[1, 40] = value
+    run = lambda n, select: {k: v.cpu().numpy() for k, v in
+                             sk.sinkhorn_forward_select(select, _t(mu), _t(n), _t(C), 0.05, 200, 1e-3).items()}
+    good, out = run(nu, "default"), run(bad, "default")
+    assert np.all(good["iters"] < 200) and out["iters"][1] == 200
+    if np.isnan(value):
+        assert np.isnan(out["marg_err"][1])
+    else:
+        assert out["marg_err"][1] >= 0.25
+    rest = [0, 2, 3]
+    for k in good:
+        np.testing.assert_array_equal(out[k][rest], good[k][rest])
