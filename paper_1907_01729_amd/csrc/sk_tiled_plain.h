@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void sk_plain_setup(TiledArgs T) {
     }
     for (int b = blockIdx.x * 256 + threadIdx.x; b < T.B; b += gridDim.x * 256) {
         T.state[b] = kPlainState;
-        P.bad[b] = 0;
+        plain_bad(P, T.B)[b] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) P.range[2] = 1;
 }
@@ -236,12 +236,12 @@ __device__ __forceinline__ void plain_product(const float *A, int lda, const flo
 template <int NW>
 __device__ __forceinline__ void plain_u(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW, false>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, P.bad, lds, wg, nwg);
+    plain_product<NW, false>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, plain_bad(P, T.B), lds, wg, nwg);
 }
 template <int NW>
 __device__ __forceinline__ void plain_v(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW, false>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, P.bad, lds, wg, nwg);
+    plain_product<NW, false>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, plain_bad(P, T.B), lds, wg, nwg);
 }
 // The first v-update.
 __global__ __launch_bounds__(512) void sk_plain_first(TiledArgs T) {
@@ -259,12 +259,12 @@ __global__ __launch_bounds__(64 * NW) void sk_plain_last(TiledArgs T) {
     extern __shared__ float lds[];
     if (!plain_taken(T)) return;
     const PlainArgs &P = T.plain;
+    int32_t *bad = plain_bad(P, T.B);
+    const int wg = (int)blockIdx.x, nwg = (int)gridDim.x;
     if (ROWS)
-        plain_product<NW, true>(P.Kt, P.l1, P.Vt, P.mut, P.mut, P.lb, P.p2, T.d1, T.B, P.bad, lds, (int)blockIdx.x,
-                                (int)gridDim.x);
+        plain_product<NW, true>(P.Kt, P.l1, P.Vt, P.mut, P.mut, P.lb, P.p2, T.d1, T.B, bad, lds, wg, nwg);
     else
-        plain_product<NW, true>(P.K, P.l2, P.Ut, P.nut, P.nut, P.lb, P.p1, T.d2, T.B, P.bad, lds, (int)blockIdx.x,
-                                (int)gridDim.x);
+        plain_product<NW, true>(P.K, P.l2, P.Ut, P.nut, P.nut, P.lb, P.p1, T.d2, T.B, bad, lds, wg, nwg);
 }
 
 // log2(mass / sum), -inf without mass, to half a unit in the last place: the
