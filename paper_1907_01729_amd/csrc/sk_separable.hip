@@ -284,6 +284,13 @@ __device__ __forceinline__ Scaled scaled_exp2(float x) {
     const float r = rintf(x);
     return {(int)r, ex2(x - r)};
 }
+// e^x of a potential as it is returned (x = -inf: none), without another
+// rounding of the size of the potential.
+__device__ __forceinline__ Scaled scaled_exp(float x) {
+    if (!(x > neg_inf())) return {kSepNone, x < 0.f ? 0.f : x};  // NaN stays NaN
+    const double y = (double)x * 1.4426950408889634, r = rint(y);
+    return {(int)r, ex2((float)(y - r))};
+}
 // mass / v, none where there is no mass.
 __device__ __forceinline__ Scaled update(float mass, Scaled v) {
     Scaled u = {__builtin_amdgcn_frexp_expf(mass) - v.h, __builtin_amdgcn_frexp_mantf(mass) * __builtin_amdgcn_rcpf(v.f)};
@@ -298,6 +305,7 @@ __device__ __forceinline__ float scaled_lg2(Scaled v) { return v.h > kSepNone ? 
 __device__ __forceinline__ float ratio(Scaled v, Scaled w) {
     return __builtin_amdgcn_ldexpf(v.f * __builtin_amdgcn_rcpf(w.f), v.h - w.h);
 }
+__device__ __forceinline__ float product(Scaled v, Scaled w) { return __builtin_amdgcn_ldexpf(v.f * w.f, v.h + w.h); }
 template <int N, class F>
 __device__ __forceinline__ void unroll(F &&f) {
     if constexpr (N > 0) {
@@ -406,9 +414,9 @@ __device__ __forceinline__ void sep_u(const SepState &S, int w, const float *sta
     }
 }
 
-// What V does beside T: nothing; v kept; v kept and the marginal error taken;
-// the error alone (no T).  The error of (the current u, the old v): its
-// columns sum to nu v_old / v_new, its rows fit.  Returns this lane's part.
+// What V does beside T: nothing; v kept; v kept and the iterate's error taken;
+// the error alone (no T).  The error of (the current u, the old v): its columns
+// sum to nu v_old / v_new, its rows fit.  Returns this lane's part.
 // v is kept in `keep` and the old v read from `old` (planes [h2][vld], the same
 // one or two), and as log2 in bout (null: none).
 enum { kVPlain = 0, kVKeep = 1, kVKeepErr = 2, kVErr = 3 };
@@ -483,6 +491,57 @@ __device__ __forceinline__ float sep_result_u(const SepState &S, int w, const i2
         if (mui > 0.f) loss = __builtin_fmaf(mui, ratio(sa, sum) + ratio(sb, sum), loss);
     }
     return loss;
+}
+
+// The marginal error of the returned potentials.  They are rounded to fp32,
+// which moves the plan's row and column sums by 2^-24 of the potentials' size, up
+// to 1e-5 in all at thousands of units; the early stop measures the iterate
+// itself, as in exact arithmetic.  Three sets of lines, once per problem:
+//   V: T of e^beta   U: the rows' error under e^alpha, and S   V: the columns'
+template <int PO, int BS>
+__device__ __forceinline__ void sep_error_T(const SepState &S, int w, const float *beta) {
+    constexpr int G = 64 / PO;
+    const int lane = S.lane, o = lane & (PO - 1);
+    for (int r0 = w * G; r0 < S.h2; r0 += kSepWaves * G) {
+        const int r = r0 + lane / PO;
+        const bool in1 = r < S.h2 && o < S.w1, in2 = r < S.h2 && o < S.w2;
+        const Scaled x = in2 ? scaled_exp(beta[r * S.w2 + o]) : none();
+        const Scaled y = line_sum<PO, BS>(S.E[kTabV2], S.Lr[kTabV2], S.yb, lane, x);
+        if (in1) put(S.plane + r * S.ld + o, y);
+    }
+}
+template <int PO, int BS>
+__device__ __forceinline__ float sep_error_rows(const SepState &S, int w, const float *alpha) {
+    constexpr int G = 64 / PO;
+    const int lane = S.lane, o = lane & (PO - 1);
+    float err = 0.f;
+    for (int c0 = w * G; c0 < S.w1; c0 += kSepWaves * G) {
+        const int c = c0 + lane / PO;
+        const bool in1 = c < S.w1 && o < S.h1, in2 = c < S.w1 && o < S.h2;
+        const int u1 = in1 ? o * S.w1 + c : 0, at = in2 ? o * S.ld + c : 0;
+        const float mui = in1 ? S.mu[u1] : 0.f;
+        const Scaled u = in1 ? scaled_exp(alpha[u1]) : none();
+        const Scaled sum = line_sum<PO, BS>(S.E[kTabU1], S.Lr[kTabU1], S.yb, lane, in2 ? get(S.plane + at) : none());
+        if (mui > 0.f) err += fabsf(product(u, sum) - mui);
+        const Scaled y = line_sum<PO, BS>(S.E[kTabU2], S.Lr[kTabU2], S.yb, lane, u);
+        if (in2) put(S.plane + at, y);
+    }
+    return err;
+}
+template <int PO, int BS>
+__device__ __forceinline__ float sep_error_cols(const SepState &S, int w, const float *beta) {
+    constexpr int G = 64 / PO;
+    const int lane = S.lane, o = lane & (PO - 1);
+    float err = 0.f;
+    for (int r0 = w * G; r0 < S.h2; r0 += kSepWaves * G) {
+        const int r = r0 + lane / PO;
+        const bool in1 = r < S.h2 && o < S.w1, in2 = r < S.h2 && o < S.w2;
+        const int u2 = in2 ? r * S.w2 + o : 0;
+        const Scaled x = in1 ? get(S.plane + r * S.ld + o) : none();
+        const Scaled sum = line_sum<PO, BS>(S.E[kTabV1], S.Lr[kTabV1], S.yb, lane, x);
+        if (in2) err += fabsf(product(scaled_exp(beta[u2]), sum) - S.nu[u2]);
+    }
+    return err;
 }
 
 // Calls f(lanes of a line, block size) with both as constants.
@@ -576,7 +635,7 @@ __global__ __launch_bounds__(64 * kSepWaves, 4) void sk_sep_solve(SepArgs T) {
     const size_t p = blockIdx.x, bplane = (size_t)T.B * T.d2p;
     S.mu = T.mu + p * T.d1;
     S.nu = T.nu + p * T.d2;
-    float *alpha = T.a + p * T.d1, *b = T.bbuf + p * T.d2p;
+    float *alpha = T.a + p * T.d1, *beta = T.beta + p * T.d2, *b = T.bbuf + p * T.d2p;
     const int n = T.n_iter;
     const bool stops = T.tol > 0.f;
     __syncthreads();
@@ -606,7 +665,7 @@ __global__ __launch_bounds__(64 * kSepWaves, 4) void sk_sep_solve(SepArgs T) {
             __syncthreads();
         }
     }
-    // The weighted tables in the place of the two that are not needed any more.
+    // The weighted tables in the place of the two that the results do not need.
     __syncthreads();
     sep_table_in(S.E[kTabU2], T.table + kTabWU * kSepTable, pu * pu);
     sep_table_in(S.E[kTabV1], T.table + kTabWV * kSepTable, pv * pv);
@@ -616,7 +675,7 @@ __global__ __launch_bounds__(64 * kSepWaves, 4) void sk_sep_solve(SepArgs T) {
     const float *bin = POMAX == 64 && stops && k < n ? b + (k & 1) * bplane : nullptr;
     i2s *tw = k & 1 ? v0 : v1;
     with_shape<POMAX>(pv, bs, [&](auto po, auto bl) {
-        sep_result_v<decltype(po)::value, decltype(bl)::value>(S, w, k & 1 ? v1 : v0, bin, tw, T.beta + p * T.d2);
+        sep_result_v<decltype(po)::value, decltype(bl)::value>(S, w, k & 1 ? v1 : v0, bin, tw, beta);
     });
     __syncthreads();
     float loss = 0.f;
@@ -624,6 +683,21 @@ __global__ __launch_bounds__(64 * kSepWaves, 4) void sk_sep_solve(SepArgs T) {
         loss = sep_result_u<decltype(po)::value, decltype(bl)::value>(S, w, tw, alpha);
     });
     loss = group_sum(loss, red);
+    // And back, for the error of what is returned.
+    sep_table_in(S.E[kTabU2], T.table + kTabU2 * kSepTable, pu * pu);
+    sep_table_in(S.E[kTabV1], T.table + kTabV1 * kSepTable, pv * pv);
+    with_shape<POMAX>(pv, bs, [&](auto po, auto bl) {
+        sep_error_T<decltype(po)::value, decltype(bl)::value>(S, w, beta);
+    });
+    __syncthreads();
+    with_shape<POMAX>(pu, bs, [&](auto po, auto bl) {
+        err = sep_error_rows<decltype(po)::value, decltype(bl)::value>(S, w, alpha);
+    });
+    __syncthreads();
+    with_shape<POMAX>(pv, bs, [&](auto po, auto bl) {
+        err += sep_error_cols<decltype(po)::value, decltype(bl)::value>(S, w, beta);
+    });
+    err = group_sum(err, red);
     if (threadIdx.x == 0) {
         T.loss[p] = (float)ldexp((double)loss / (double)T.s, kSepWeight);
         T.merr[p] = err;

@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import paper_1907_01729_amd as sk
+import workloads
 from parity_util import gauge_fixed_errors, loss_rel_err
 
 pytestmark = pytest.mark.gpu
@@ -141,6 +142,44 @@ def test_cost_left_to_the_sweeps(case):
     out = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, 170)
     ref = oracle.forward(mu, nu, C[None], lam, 170)
     assert loss_rel_err(out["loss"].cpu().numpy(), ref["loss"]) <= 1e-4
+
+
+def returned_error(g, mu, nu, C, lam, side):
+    """||P 1 - mu||_1 + ||P^T 1 - nu||_1 of the returned potentials, in 64 bits, with the library's fp32 scale of the
+    cost, log2(e) / lam, and the cost that splits: the sum of the entries of its first rows and columns."""
+    s = np.float64(np.float32(1.4426950408889634) / np.float32(lam)) * np.log(2.0)
+    D = C.astype(np.float64).reshape(side, side, side, side)
+    D = D[:, :1, :, :1] + D[:1, :, :1, :] - D[0, 0, 0, 0]
+    D = D.reshape(C.shape)
+    out = []
+    for b in range(mu.shape[0]):
+        P = np.exp(g["alpha"][b].astype(np.float64)[:, None] + g["beta"][b].astype(np.float64)[None, :] - s * D)
+        out.append(np.abs(P.sum(1) - mu[b]).sum() + np.abs(P.sum(0) - nu[b]).sum())
+    return np.array(out)
+
+
+@pytest.mark.parametrize("side, lam, tol, n_iter", [
+    (28, 0.01, 0.0, 300),     # converged below the rounding of the potentials
+    (32, 0.002, 2e-6, 2000),  # a tolerance below that rounding
+    (28, 0.02, 2e-5, 2000),   # and above it
+    (40, 0.004, 2e-6, 2000),  # lines of up to 64 entries: one plane of v
+    (40, 0.004, 0.0, 700),
+])
+def test_split_marginal_error_is_the_returned_iterates(side, lam, tol, n_iter):
+    """marg_err speaks of the returned fp32 potentials, their rounding included; the early stop of the iterate, as the
+    oracle's does."""
+    p = workloads.image(seed=21, B=8, side=side, n_iter=n_iter, lam=lam)
+    mu, nu, C = p.mu, p.nu, p.C[0]
+    assert "sk_sep_solve" in sk.sinkhorn_describe(8, side ** 2, side ** 2, 0, lam, n_iter, tol)
+    g = {k: v.cpu().numpy() for k, v in sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, n_iter, tol).items()}
+    true = returned_error(g, mu, nu, C, lam, side)
+    print(f"[split] side={side} lam={lam} tol={tol} iters {g['iters']} reported {g['marg_err']} true {true}",
+          file=sys.stderr, flush=True)
+    # the line sums' own rounding: a few 2^-24 of a unit mass on either side
+    assert np.all(np.abs(g["marg_err"] - true) <= 2e-7 + 1e-3 * true)
+    if tol == 2e-5:
+        free = oracle.forward(mu, nu, C[None], lam, n_iter, tol=tol)
+        assert np.all(np.abs(free["iters"] - g["iters"]) <= 1)
 
 
 @pytest.mark.parametrize("value", [np.nan, -0.25])
