@@ -117,8 +117,9 @@ SK_API sk_status sinkhorn_forward(const sk_problem *p, const float *mu, const fl
  * Diagnostic variant of sinkhorn_forward for tests and measurements: the
  * same arguments, plus a selector that pins which kernels run.
  *   SK_SELECT_DEFAULT        exactly sinkhorn_forward;
- *   SK_SELECT_LOG_ONLY       resident shapes: the log-domain kernel alone
- *                            (no plain-form attempt);
+ *   SK_SELECT_LOG_ONLY       the log-domain kernels alone (no plain-form
+ *                            attempt, and in the tiled regime no solve by line
+ *                            sums of a cost that splits);
  *   SK_SELECT_PLAIN_ONLY     resident shapes: the first-choice plain-form
  *                            kernel alone, without its log-domain fallback:
  *                            a problem it cannot keep in range comes back

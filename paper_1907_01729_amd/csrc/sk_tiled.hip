@@ -2299,6 +2299,13 @@ bool plain_wanted(const FwdArgs &a, int W, size_t floats, PlainArgs *P) {
     return need <= floats;
 }
 
+// Whether the device is asked if the cost splits over two axes; `bytes` of
+// column partials take its tables.
+bool separable_wanted(const FwdArgs &a, int B, int kind, size_t bytes, SepArgs *P) {
+    return kind == kKindShared && a.n_iter > 0 && a.select != SK_SELECT_LOG_ONLY &&
+           separable_plan(B, a.d1, a.d2, a.n_iter, bytes, P);
+}
+
 // One chunk (at most kTiledMaxBatch problems) of the forward.
 hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
     Layout L;
@@ -2320,8 +2327,7 @@ hipError_t launch_tiled_chunk(const FwdArgs &a, void *ws, hipStream_t st) {
     // the column partials (if it does not split, they are not read again), the
     // mode lies beside the stop counters.
     SepArgs sep;
-    if (kind == kKindShared && a.n_iter > 0 &&
-        separable_plan(a.B, a.d1, a.d2, a.n_iter, sizeof(float) * 2 * (size_t)T.R * T.B * T.d2p, &sep)) {
+    if (separable_wanted(a, a.B, kind, sizeof(float) * 2 * (size_t)T.R * T.B * T.d2p, &sep)) {
         sep.mode = T.sync + 1;
         sep.table = T.part;
         sep.mu = T.mu;
@@ -2419,8 +2425,8 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
     else
         snprintf(mrg, sizeof mrg, "the merge folded into the next sweep");
     SepArgs sep;
-    const bool split = kind == kKindShared && a.n_iter > 0 &&
-                       separable_plan(B, a.d1, a.d2, a.n_iter, sizeof(float) * 2 * (size_t)R * B * padded_width(a.d2, kind), &sep);
+    const bool split =
+        separable_wanted(a, B, kind, sizeof(float) * 2 * (size_t)R * B * padded_width(a.d2, kind), &sep);
     PlainArgs plain;
     const bool prod = kind == kKindShared && R * B >= 4 &&
                       plain_wanted(a, W, 2 * (size_t)R * B * padded_width(a.d2, kind), &plain);

@@ -200,3 +200,17 @@ def test_split_bad_mass_reaches_the_marginal_error(value):
     rest = [0, 2, 3]
     for k in good:
         np.testing.assert_array_equal(out[k][rest], good[k][rest])
+
+
+def test_log_selector_reaches_the_sweeps():
+    mu, nu, C = make(23, 8, (14, 14), (14, 14), "sq")
+    assert "sk_sep_solve" in sk.sinkhorn_describe(8, 196, 196, 0, 0.03, 170)
+    line = sk.sinkhorn_describe(8, 196, 196, 0, 0.03, 170, select="log")
+    assert "sk_sep_solve" not in line and "matrix products" not in line
+    solve = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), 0.03, 170)
+    sweeps = sk.sinkhorn_forward_select("log", _t(mu), _t(nu), _t(C), 0.03, 170)
+    ref = oracle.forward(mu, nu, C[None], 0.03, 170)
+    for out in (solve, sweeps):
+        g = {k: v.cpu().numpy() for k, v in out.items()}
+        assert loss_rel_err(g["loss"], ref["loss"]) <= 1e-5
+    assert not torch.equal(solve["alpha"], sweeps["alpha"])  # other arithmetic: it was the sweeps that ran
