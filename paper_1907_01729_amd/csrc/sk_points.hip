@@ -54,9 +54,8 @@ __device__ __forceinline__ float cl_cell(const float *x, const float *y, int D, 
 
 // grad_x: one wavefront per row i (and problem b, or the whole batch for
 // shared clouds); lanes stride over j; D <= kPointsGradD accumulators per lane.
-// grad_y is the same kernel with the roles of the clouds swapped (a kernel of
-// its own, one lane per column running down all the rows, took 1134 us for one
-// pair of 2000 points where this takes 29).
+// grad_y is the same kernel with the roles of the clouds swapped, or
+// sk_points_grad_y (see grad_y_by_columns).
 __global__ __launch_bounds__(kPtThreads) void sk_points_grad_x(PointsBwdArgs A) {
     const int lane = threadIdx.x & 63;
     const size_t wid = (size_t)blockIdx.x * (kPtThreads / 64) + (threadIdx.x >> 6);
@@ -89,9 +88,49 @@ __global__ __launch_bounds__(kPtThreads) void sk_points_grad_x(PointsBwdArgs A) 
     }
 #pragma unroll
     for (int k = 0; k < kPointsGradD; ++k) {
+        if (k >= D) break;
         const float v = wave_sum(acc[k]);
-        if (k < D && lane == 0) A.grad_X[wid * D + k] = v;
+        if (lane == 0) A.grad_X[wid * D + k] = v;
     }
+}
+
+// grad_y: lanes = 64 columns j (one wavefront per column block and problem,
+// or the whole batch for shared clouds); rows summed in order.
+__global__ __launch_bounds__(kPtThreads) void sk_points_grad_y(PointsBwdArgs A) {
+    const int lane = threadIdx.x & 63;
+    const int JB = (A.d2 + 63) / 64;
+    const size_t wid = (size_t)blockIdx.x * (kPtThreads / 64) + (threadIdx.x >> 6);
+    const size_t nw = (size_t)(A.batched ? A.B : 1) * JB;
+    if (wid >= nw) return;
+    const int bx = (int)(wid / JB);
+    const int j = (int)(wid % JB) * 64 + lane;
+    if (j >= A.d2) return;
+    const int D = A.D;
+    const float *y = A.Y + ((size_t)bx * A.d2 + j) * D;
+    float acc[kPointsGradD];
+#pragma unroll
+    for (int k = 0; k < kPointsGradD; ++k) acc[k] = 0.f;
+    const int b0 = A.batched ? bx : 0, b1 = A.batched ? bx + 1 : A.B;
+    for (int b = b0; b < b1; ++b) {
+        const float g = 2.f * A.grad_loss[b];
+        const float bj = A.beta[(size_t)b * A.d2 + j] * kLog2e;
+        const float *Xb = A.X + (size_t)bx * A.d1 * D;
+        float part[kPointsGradD];
+#pragma unroll
+        for (int k = 0; k < kPointsGradD; ++k) part[k] = 0.f;
+        for (int i = 0; i < A.d1; ++i) {
+            const float *x = Xb + (size_t)i * D;
+            const float p = ex2(__builtin_fmaf(A.alpha[(size_t)b * A.d1 + i], kLog2e, bj) + cl_cell(x, y, D, A.rs));
+#pragma unroll
+            for (int k = 0; k < kPointsGradD; ++k)
+                if (k < D) part[k] = __builtin_fmaf(p, y[k] - x[k], part[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < kPointsGradD; ++k) acc[k] = __builtin_fmaf(g, part[k], acc[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kPointsGradD; ++k)
+        if (k < D) A.grad_Y[((size_t)bx * A.d2 + j) * D + k] = acc[k];
 }
 
 // One side's point gradient for per-sample clouds, as a sweep over that
@@ -223,6 +262,24 @@ hipError_t launch_points_cost(const float *X, const float *Y, float *C, int nb, 
     return hipGetLastError();
 }
 
+// One lane per column, running down all the rows, for grad_y.  It takes
+// ceil(d2 / 64) d1 steps of a wavefront per pair of clouds, the row kernel d2
+// ceil(d1 / 64) and D wavefront sums per column, so it is the better one where
+// wavefronts are many and the rows few (measured, gradients of both sides, by
+// columns and by rows: 16384 clouds of 20 x 64 points in 4 dimensions 418 and 736
+// us, 8192 of 33 x 65 in 6, equal steps, 489 and 553); elsewhere its lanes run through a long
+// chain (4 clouds of 2000 x 2000 in 8 dimensions: 4270 us, by rows 924; one pair
+// of 2000: 1134 and 29) or hold too many coordinates (8192 of 60 x 60 in 16: 3911
+// and 3402).  Also where a wavefront per column would not fit a grid.
+bool grad_y_by_columns(const PointsBwdArgs &a) {
+    if (!a.batched) return false;
+    const int64_t waves = (int64_t)a.B * ((a.d2 + 63) / 64);
+    const int64_t cols = (int64_t)((a.d2 + 63) / 64) * a.d1, rows = (int64_t)a.d2 * ((a.d1 + 63) / 64);
+    if ((int64_t)a.B * a.d2 >= (1 << 26)) return true;
+    return (waves >= 2000 && a.d1 <= (a.D <= 8 ? 200 : 32) && 10 * cols <= 11 * rows) ||
+           (waves >= 1000 && 2 * cols <= rows);
+}
+
 hipError_t launch_points_grads(const PointsBwdArgs &a, hipStream_t st) {
     // Per-sample clouds (or one pair) with few coordinates: row sweeps with the
     // other side in registers (both sides at most 2048 points).
@@ -237,7 +294,10 @@ hipError_t launch_points_grads(const PointsBwdArgs &a, hipStream_t st) {
         const size_t waves = nb * a.d1;
         hipLaunchKernelGGL(sk_points_grad_x, dim3((waves + wpb - 1) / wpb), dim3(kPtThreads), 0, st, a);
     }
-    if (a.grad_Y) {
+    if (a.grad_Y && grad_y_by_columns(a)) {
+        const size_t waves = nb * ((a.d2 + 63) / 64);
+        hipLaunchKernelGGL(sk_points_grad_y, dim3((waves + wpb - 1) / wpb), dim3(kPtThreads), 0, st, a);
+    } else if (a.grad_Y) {
         PointsBwdArgs t = a;
         t.X = a.Y;
         t.Y = a.X;

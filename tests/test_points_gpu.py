@@ -186,3 +186,15 @@ def test_points_batch_above_grid_limit():
     against the oracle, with the point gradients."""
     prob = workloads.random_points(seed=93, B=65537, d1=130, d2=8, D=3, lam=0.2, n_iter=30)
     check_points(prob, idx=np.array([0, 65534, 65535, 65536]))
+
+
+@pytest.mark.parametrize("B, d1, d2, D", [
+    (2048, 20, 64, 4),   # grad_Y by columns
+    (1100, 10, 65, 9),   # few rows, more coordinates
+    (2048, 70, 33, 5),   # by rows (two wavefront steps for 70 rows, half the lanes for 33 columns)
+    (300, 40, 50, 8),    # by rows: few wavefronts
+])
+def test_points_gradient_by_columns_and_rows(B, d1, d2, D):
+    """Both kernels of the second cloud's gradient, on either side of their rule; oracle on five problems."""
+    prob = workloads.random_points(500 + d1, B=B, d1=d1, d2=d2, D=D, lam=0.4, n_iter=20)
+    check_points(prob, idx=np.array([0, 1, 63, 64, B - 1]))
