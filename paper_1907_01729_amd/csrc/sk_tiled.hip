@@ -1817,17 +1817,20 @@ int tiled_kind(int d2, int c_batched) {
 
 // Which sweep serves a problem: the shared-cost sweep with W problems per
 // work-group when C is shared and the batch fills at least four wavefronts, or
-// the rows are wider than 2048, otherwise one problem per work-group.  (The
+// the rows are wide and many, otherwise one problem per work-group.  (The
 // widest one-problem sweep keeps a quarter of its row in accumulation
 // registers and loads the cost beside the arithmetic: one problem of 4096 x
 // 4096 took 84 us per iteration, in the shared-cost sweep, three wavefronts of
-// four idle, 35.  At 1600 columns it is 14.1 against 17.4.  More rows than 256
-// row blocks of 64 kSegs hold would take more row blocks, and their partials
-// more workspace, than the one-problem sweep.)
+// four idle, 35.  At 1600 columns it is 14.1 against 17.4.  Fewer than 300 rows
+// of fewer than 2900 columns, half of the widest row's registers being padding,
+// do not fill it: 60 iterations of 109 x 2405 take 0.98 ms here and 1.19 there,
+// 300 x 2405 1.13 each way, 50 x 2900 0.95.  More rows than 256 row blocks of 64
+// kSegs hold would take more row blocks, and their partials more workspace, than
+// the one-problem sweep.)
 int shared_width(int B, int d1, int d2, int kind) {
     if (kind != kKindShared) return 0;
     if (B >= 8) return 8;
-    if (B >= 4 || (d2 > 2048 && d1 <= 256 * 64 * kSegs)) return 4;
+    if (B >= 4 || (d2 > 2048 && (d2 >= 2900 || d1 >= 300) && d1 <= 256 * 64 * kSegs)) return 4;
     return 0;
 }
 

@@ -175,6 +175,14 @@ def test_few_wide_problems_fit_the_library_scratch(B, d1):
     assert sk.sinkhorn_workspace_bytes(B, d1, 4096, 0, 0.1, 10) <= sk.NOALLOC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("B, d1, d2, shared", [
+    (3, 299, 2899, False), (3, 300, 2049, True), (1, 20, 2900, True), (2, 5000, 2048, False), (4, 299, 2899, True),
+])
+def test_few_wide_problems_take_the_faster_sweep(B, d1, d2, shared):
+    line = sk.sinkhorn_describe(B, d1, d2, 0, 0.1, 10)
+    assert ("sk_tiled_sweep_shared<" in line) == shared and "sk_tiled_sweep" in line
+
+
 @pytest.mark.parametrize("d2, merge", [(65536, "rows"), (65537, "cols"), (2097152, "cols"), (1 << 24, "cols")])
 def test_merge_slices_of_the_widest_rows(d2, merge):
     # The early stop counts a problem's slices in 15 bits, and they are a grid dimension: at most 16384 (the widest

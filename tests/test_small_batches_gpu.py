@@ -26,8 +26,11 @@ def _t(x):
     (8, 300, 517, False, 2e-4, "rows"),  # compacted batch, split stop test
     (4, 259, 1030, False, 2e-4, "rows"),
     (3, 700, 250, True, 2e-4, "rows"),
-    (1, 70, 2100, False, 0.0, "cols"),   # wide rows, one problem of four wavefronts
+    (1, 70, 2100, False, 0.0, "cols"),   # wide rows, too few for the shared-cost sweep
     (3, 150, 2305, False, 1e-3, "rows"),
+    (1, 300, 2100, False, 0.0, "rows"),  # enough rows for the shared-cost sweep
+    (3, 301, 2305, False, 1e-3, "rows"),
+    (2, 70, 2901, False, 0.0, "cols"),
 ])
 def test_small_batch(B, d1, d2, batched, tol, merge):
     p = workloads.random_problem(900 + d1, B, d1, d2, 0.02 if d2 < 2000 else 0.05, 40, c_batched=batched,
