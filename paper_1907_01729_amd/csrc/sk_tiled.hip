@@ -276,11 +276,36 @@ __device__ float col_lse_exact(const TiledArgs &T, int b, int j) {
 }
 
 // Merge of the row blocks' (max, sumexp) partials of the first v-update: beta
-// of iteration 1.  A work-group takes 64 columns; its 16 wavefronts each run
-// through every 16th row block, several loads in flight, and their pairs are
-// combined in wavefront order.  (One wavefront per 64 columns running through
-// all the row blocks waited for every load in turn: 48 us at 75 row blocks.)
+// of iteration 1.  A work-group takes 64 columns.
+//
+// Up to 16 row blocks: one wavefront loads every pair at once.  More: each of 16
+// wavefronts runs through every 16th row block, several loads in flight, and
+// their pairs are combined in wavefront order.  (One wavefront running through
+// all the row blocks waited for every load in turn: 48 us at 75 row blocks.
+// With few of them the 16 wavefronts are mostly idle and are themselves the
+// work: 600 problems of 20 x 5000, 5 row blocks each, 3 iterations 595 -> 497 us.)
 constexpr int kMergeExactWaves = 16;
+__device__ __forceinline__ void exact_beta(const TiledArgs &T, int b, int j, float M, float S) {
+    const float nuj = T.nu[(size_t)b * T.d2 + j];
+    T.bbuf[(size_t)1 * T.B * T.d2p + (size_t)b * T.d2p + j] =
+        nuj > 0.f ? log2f(nuj) - (M + lg2(S)) : neg_inf();
+}
+__global__ __launch_bounds__(64) void sk_tiled_merge_exact_few(TiledArgs T) {
+    if (splits(T) || plain_taken(T)) return;
+    const int j = blockIdx.x * kMergeThreads + threadIdx.x, b = blockIdx.y;
+    if (j >= T.d2) return;
+    float m[kMergeExactWaves], s[kMergeExactWaves], M = kNegBig, S = 0.f;
+#pragma unroll
+    for (int r = 0; r < kMergeExactWaves; ++r) {
+        m[r] = r < T.R ? T.part[pidx(T, 0, r, b, j)] : kNegBig;
+        s[r] = r < T.R ? T.part[pidx(T, 1, r, b, j)] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < kMergeExactWaves; ++r) M = fmaxf(M, m[r]);
+#pragma unroll
+    for (int r = 0; r < kMergeExactWaves; ++r) S += s[r] * ex2(m[r] - M);
+    exact_beta(T, b, j, M, S);
+}
 __global__ __launch_bounds__(64 * kMergeExactWaves) void sk_tiled_merge_exact(TiledArgs T) {
     if (splits(T) || plain_taken(T)) return;
     __shared__ float pm[kMergeExactWaves][64], ps[kMergeExactWaves][64];
@@ -310,13 +335,10 @@ __global__ __launch_bounds__(64 * kMergeExactWaves) void sk_tiled_merge_exact(Ti
     ps[w][lane] = S;
     __syncthreads();
     if (w != 0 || !in) return;
-    const int n = min(T.R, kMergeExactWaves);
-    for (int q = 1; q < n; ++q) M = fmaxf(M, pm[q][lane]);
+    for (int q = 1; q < kMergeExactWaves; ++q) M = fmaxf(M, pm[q][lane]);
     S = 0.f;
-    for (int q = 0; q < n; ++q) S += ps[q][lane] * ex2(pm[q][lane] - M);
-    const float nuj = T.nu[(size_t)b * T.d2 + j];
-    T.bbuf[(size_t)1 * T.B * T.d2p + (size_t)b * T.d2p + j] =
-        nuj > 0.f ? log2f(nuj) - (M + lg2(S)) : neg_inf();
+    for (int q = 0; q < kMergeExactWaves; ++q) S += ps[q][lane] * ex2(pm[q][lane] - M);
+    exact_beta(T, b, j, M, S);
 }
 
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -1972,6 +1994,12 @@ void launch_col_exact(const TiledArgs &T, hipStream_t st) {
     else
         hipLaunchKernelGGL(sk_tiled_col_exact<1>, dim3(T.JC, T.R, T.B), dim3(kMergeThreads), 0, st, T);
 }
+void launch_merge_exact(const TiledArgs &T, hipStream_t st) {
+    if (T.R <= kMergeExactWaves)
+        hipLaunchKernelGGL(sk_tiled_merge_exact_few, dim3(T.JC, T.B), dim3(64), 0, st, T);
+    else
+        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
+}
 // MS = ceil(d2 / 1024) work-groups of 256 threads per problem, plus the relist
 // work-group of a compacted batch.
 void launch_merge(const TiledArgs &T, int k, hipStream_t st) {
@@ -1998,7 +2026,7 @@ hipError_t run_wide(const TiledArgs &T, hipStream_t st) {
     hipLaunchKernelGGL(sk_tiled_init, dim3(512), blk, 0, st, T);
     if (T.n_iter > 0) {
         launch_col_exact(T, st);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
+        launch_merge_exact(T, st);
         for (int k = 1; k <= T.n_iter; ++k) {
             hipLaunchKernelGGL(sk_wide_rows<false>, rg, rblk, 0, st, T, k);
             hipLaunchKernelGGL(sk_wide_cols<false>, cg, blk, 0, st, T, k);
@@ -2027,7 +2055,7 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
             hipLaunchKernelGGL(sk_plain_setup, dim3(512), dim3(256), 0, st, T);
         }
         launch_col_exact(T, st);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
+        launch_merge_exact(T, st);
         if (T.plain.range)
             hipLaunchKernelGGL(sk_plain_first, dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
         for (int k = 1; k <= T.n_iter; ++k) {
@@ -2063,7 +2091,7 @@ hipError_t run_stream(const TiledArgs &T, hipStream_t st) {
     hipLaunchKernelGGL(sk_tiled_init, dim3(512), dim3(kThreads), 0, st, T);
     if (T.n_iter > 0) {
         launch_col_exact(T, st);
-        hipLaunchKernelGGL(sk_tiled_merge_exact, dim3(T.JC, T.B), dim3(64 * kMergeExactWaves), 0, st, T);
+        launch_merge_exact(T, st);
         for (int k = 1; k <= T.n_iter; ++k)
             hipLaunchKernelGGL((sk_tiled_sweep_stream<NC4, false>), grid, blk, lds, st, T, k);
     }

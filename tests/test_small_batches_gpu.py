@@ -31,6 +31,8 @@ def _t(x):
     (1, 300, 2100, False, 0.0, "rows"),  # enough rows for the shared-cost sweep
     (3, 301, 2305, False, 1e-3, "rows"),
     (2, 70, 2901, False, 0.0, "cols"),
+    (1, 64, 200, False, 0.0, "cols"),    # 16 row blocks: the exact merge of one wavefront
+    (1, 68, 200, False, 0.0, "cols"),    # 17: of 16
 ])
 def test_small_batch(B, d1, d2, batched, tol, merge):
     p = workloads.random_problem(900 + d1, B, d1, d2, 0.02 if d2 < 2000 else 0.05, 40, c_batched=batched,
