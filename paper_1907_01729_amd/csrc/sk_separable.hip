@@ -591,9 +591,10 @@ __device__ __forceinline__ float group_sum(float v, float *red) {
 // its K iterations: the launches that follow skip it.
 // Bound by the chain of its line sums (LDS round trips and two barriers per
 // iteration; 16 wavefronts on one CU) and, for 64-entry lines in blocks of 4,
-// by vector issue.  Measured per iteration: 3.2 us for up to 256 problems of
-// 28 x 28 (sweep and merge before: 50.9), 23 us for 64 problems of 64 x 64
-// (236.9), where the rest of a call is the two empty launches per iteration.
+// by vector issue.  Measured per iteration: 3.1 us for up to 256 problems of
+// 28 x 28 (sweep and merge before: 50.9), 21 us for 64 problems of 64 x 64
+// (236.9).  The rest of a call is the two empty launches per iteration, 3.3 to
+// 5.4 us: more than the solve where problems are small (28 x 28: 4.0 of 7.1).
 __device__ __forceinline__ void sep_table_in(float *dst, const float *src, int n) {
     for (int u = threadIdx.x; u < n / 4; u += 64 * kSepWaves)
         reinterpret_cast<f4s *>(dst)[u] = reinterpret_cast<const f4s *>(src)[u];
@@ -725,9 +726,12 @@ bool separable_plan(int B, int d1, int d2, int n_iter, size_t table_bytes, SepAr
     if (table_bytes < kTables * sizeof(float) * kSepTable) return false;
     // Both sides measured on the MI355X, in microseconds.  An iteration of the
     // sweeps: 10 for its two launches and 1 per 4.5e6 cells of the batch.  Of
-    // the solve: 1.5 and 41e-6 per half cell of a problem (28 x 28: 3.2, 64 x
-    // 64: 23) for every 256 problems (one work-group per CU), and 3.5 for the
-    // two empty launches.  The test of the cost, when it fails: 16, and one
+    // the solve: 1.2 and 38e-6 per half cell of a problem (14 x 14: 1.2, 28 x 28:
+    // 3.1, 64 x 64: 21.0 in blocks of 4, 16.2 in blocks of 16) for every 256
+    // problems (one work-group per CU), and for the two empty launches 3.3 to 5.4
+    // (whole calls' time per iteration less the solve's), taken as 3.8: at the
+    // line the solve is ahead, 40 x 40, two problems, 13.1 and 15.1; 64 x 64, five
+    // problems, 24.3 and 50.1.  The test of the cost, when it fails: 16, and one
     // read of the cost; it must stay below 1 % of the sweeps.
     const double cells = (double)d1 * d2, sweeps = 10.0 + cells * B / 4.5e6;
     if (n_iter * sweeps < 100.0 * (16.0 + cells / 1e6)) return false;
@@ -743,7 +747,7 @@ bool separable_plan(int B, int d1, int d2, int n_iter, size_t table_bytes, SepAr
             most = most > half ? most : half;
         }
     }
-    if (!most || 3.5 + (1.5 + 41e-6 * most) * ((B + 255) / 256) >= sweeps) return false;
+    if (!most || 3.8 + (1.2 + 38e-6 * most) * ((B + 255) / 256) >= sweeps) return false;
     return true;
 }
 
