@@ -92,7 +92,17 @@ SK_API size_t sinkhorn_workspace_bytes(const sk_problem *p);
  * per sample: both products); a problem whose scaled cost spans more than
  * 64 bits, or whose sums or scalings leave a guarded fp32 range at any
  * iteration, is re-solved from the start in the log domain by the same
- * work-group.  Every problem is solved: iters >= 0.
+ * work-group.
+ *
+ * Larger supports with a shared C may take other forms of the same iterates,
+ * as the device finds out in every call: a C that splits over two axes
+ * (C[(r, c), (r', c')] = A[r, r'] + B[c, c'], every entry to fp32 rounding) is
+ * solved by line sums, one work-group per problem; without an early stop or a
+ * warm start, a C whose scaled span is at most 64 bits by the plain form as
+ * matrix products, a problem whose sums leave a guarded range being re-solved
+ * in the log domain.  Everything else, and per-sample costs, run the
+ * log-domain sweeps.  sinkhorn_describe names what a problem may take.
+ * Every problem is solved: iters >= 0.
  *
  *   mu        [B, d1]              input histograms
  *   nu        [B, d2]
@@ -100,7 +110,12 @@ SK_API size_t sinkhorn_workspace_bytes(const sk_problem *p);
  *   alpha     [B, d1]   out        log u of the returned iterate
  *   beta      [B, d2]   out        log v of the returned iterate
  *   loss      [B]       out        E^0 = sum_ij P_ij C_ij (Section 5)
- *   marg_err  [B]       out        ||P 1 - mu||_1 + ||P^T 1 - nu||_1
+ *   marg_err  [B]       out        ||P 1 - mu||_1 + ||P^T 1 - nu||_1 of the
+ *                                  returned alpha and beta; their rounding to
+ *                                  fp32 is part of it (about 2^-23 times the
+ *                                  potentials' size), so it may lie above tol
+ *                                  by that much where the early stop, which
+ *                                  measures the iterate, fired
  *   iters     [B] int32 out        iterations run per sample (n_iter unless
  *                                  the early stop fired)
  *   workspace, ws_bytes            device scratch of at least
@@ -157,7 +172,8 @@ SK_API sk_status sinkhorn_forward_select(const sk_problem *p, int32_t select, co
  * whole state: continuing a K-iteration forward from its alpha for n more
  * iterations gives the iterates of a (K + n)-iteration forward, up to
  * rounding.  alpha0 may be the alpha output buffer itself (read before it is
- * written).  Runs the log-domain kernels (the plain form starts from u = 1).
+ * written).  Runs the log-domain kernels (the plain form starts from u = 1),
+ * or the line sums of a C that splits over two axes.
  * Arguments, workspace and errors as sinkhorn_forward; alpha0 NULL:
  * SK_ERR_NULLPTR.
  */
@@ -306,8 +322,9 @@ SK_API const char *sinkhorn_status_string(sk_status s);
  * Which kernel family sinkhorn_forward uses for *p:
  *   1 = resident (max(d1, d2) <= 128: C and potentials on-chip for the whole
  *       iteration; plain form with the log-domain fallback described above),
- *   2 = tiled sweep (one pass over C per iteration, column partials merged
- *       across row blocks).
+ *   2 = tiled (C in memory: one pass over it per iteration, column partials
+ *       merged across row blocks, or one of the forms described above; two
+ *       passes for rows wider than 4096).
  * Returns 0 for an invalid problem.
  */
 SK_API int32_t sinkhorn_regime(const sk_problem *p);
