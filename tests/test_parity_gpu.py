@@ -418,9 +418,8 @@ def test_image_reduced_batch():
 
 
 def test_image_full_batch_sampled():
-    """The full image workload (B=256, d=784, 300 iterations); the oracle
-    checks problems from four different 8-problem work-groups (0, 9, 16, 31)
-    and both ends of the batch."""
+    """The full image workload (B=256, d=784, 300 iterations, solved by line
+    sums); the oracle checks problems across the batch and both its ends."""
     prob = workloads.make_config(3)
     gpu = _gpu(prob)
     idx = np.array([0, 77, 130, 255])
@@ -445,8 +444,8 @@ def grid_full():
 
 @pytest.mark.parametrize("b", [0, 8, 63])
 def test_grid_full_size_sampled(grid_full, b):
-    """The full grid workload; the oracle (about 35 s per problem) checks
-    problems from the first, second and last 8-problem work-group."""
+    """The full grid workload (solved by line sums); the oracle (about 35 s per
+    problem) checks problems across the batch."""
     prob, gpu = grid_full
     # tol = 1e-6 is out of reach in 500 iterations at lambda = 1e-3 (the fp64
     # marginal error is ~6e-4 there), so every problem runs all iterations.
@@ -561,9 +560,11 @@ def test_shared_sweep_multi_segment_rows():
 
 
 def test_shared_sweep_small_lambda_exact_rows():
-    """lambda = 1e-3 on a 24x24 grid with a batch of 8 (shared-cost sweep):
-    rows whose shifted sums leave [2^-64, 2^64] take the exact logsumexp."""
+    """lambda = 1e-3 on a 24x24 grid with a batch of 8 (shared-cost sweep,
+    pinned): rows whose shifted sums leave [2^-64, 2^64] take the exact
+    logsumexp."""
     prob = workloads.make_config(4, B=8, side=24, n_iter=120)
+    set_form("log")
     gpu, ref = check_forward(prob, merr_atol=1e-4)
     check_backward(prob, gpu, ref)
 
@@ -602,21 +603,58 @@ def test_stream_small_lambda_exact_paths():
 
 # ---------------------------------------------------------------- early stop with batch compaction (shared sweep)
 
+def _l2(prob):
+    """The workload with the plain grid distance: a cost that does not split over the axes, so that the shared-cost
+    sweep runs (sk_sep_solve takes the squared one)."""
+    prob.C = np.sqrt(prob.C.astype(np.float64)).astype(np.float32)
+    prob.name += "_l2"
+    return prob
+
+
 def test_shared_sweep_early_stop_compaction():
     """Image histograms with an early stop: problems stop at different
     iterations; the shared-cost sweep compacts the running problems into its
     8-problem work-groups.  Parity with the oracle at the GPU's iteration
-    counts, and the same bits as without compaction."""
-    prob = workloads.make_config(3, B=24, side=20, n_iter=400)
+    counts, and the same bits as without compaction and as the log-domain
+    selector (it is the sweep that ran)."""
+    prob = _l2(workloads.make_config(3, B=24, side=20, n_iter=400))
     prob.tol = 2e-4
     set_form("nocompact")
     plain = _gpu(prob)
+    set_form("log")
+    log = _gpu(prob)
     set_form("default")
     gpu, ref = check_forward(prob)
     its = gpu["iters"]
     assert (its < prob.n_iter).sum() >= prob.B - 2 and len(set(its.tolist())) > 3, its
     for k in plain:
         np.testing.assert_array_equal(gpu[k], plain[k])
+        np.testing.assert_array_equal(gpu[k], log[k])
+
+
+def test_split_cost_early_stop_small_images():
+    """The squared distance on the same images (line sums): parity at the GPU's counts."""
+    prob = workloads.make_config(3, B=24, side=20, n_iter=400)
+    prob.tol = 2e-4
+    gpu, ref = check_forward(prob)
+    its = gpu["iters"]
+    assert (its < prob.n_iter).sum() >= prob.B - 2 and len(set(its.tolist())) > 3, its
+
+
+@pytest.mark.parametrize("config, idx, n_iter", [(3, [0, 77, 255], 300), (4, [9], 250)])
+def test_shared_sweep_full_size_sampled(config, idx, n_iter):
+    """The shared-cost sweep at 784 and 4096 columns over hundreds of iterations at small lambda (a plain grid distance,
+    C / lambda up to 138 and 1400), full batches; the same bits as the log-domain selector."""
+    prob = _l2(workloads.make_config(config, n_iter=n_iter))
+    prob.tol = 0.0
+    gpu = _gpu(prob)
+    set_form("log")
+    log = _gpu(prob)
+    for k in gpu:
+        np.testing.assert_array_equal(gpu[k], log[k])
+    idx = np.array(idx)
+    gpu, ref = check_forward(prob, gpu=gpu, idx=idx, merr_atol=1e-4)
+    check_backward(prob, gpu, ref, idx=idx)
 
 
 def test_split_merge_early_stop():

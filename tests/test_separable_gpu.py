@@ -126,22 +126,49 @@ def test_widest_lines():
         assert float((x - y).norm() / y.norm()) <= 5e-6, k
 
 
-@pytest.mark.parametrize("case", ["entry", "spread", "nan"])
+# One entry moved by 1, where plan has mass: rows and columns in the first work-groups of the cost's test, in late ones,
+# and the last entry.
+ENTRIES = [(0, 1), (77, 101), (130, 127), (195, 195)]
+
+
+@pytest.mark.parametrize("case", ENTRIES + ["spread", "nan"])
 def test_cost_left_to_the_sweeps(case):
     mu, nu, C = make(16, 3, (14, 14), (14, 14), "sq")
-    lam = 0.03
-    if case == "entry":
-        C[77, 101] += 1e-3
-    elif case == "spread":
-        lam = 3e-4  # 4 neighbours span more than 150 bits
+    lam, split = 0.03, C.copy()
     if case == "nan":
         C[77, 101] = np.nan
         out = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, 170)
         assert torch.isnan(out["loss"]).all()
         return
-    out = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, 170)
+    if case == "spread":
+        lam = 3e-4  # 4 neighbours span more than 150 bits
+    else:
+        C[case] -= 1.0
+    out = {k: v.cpu().numpy() for k, v in sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), lam, 170).items()}
+    log = {k: v.cpu().numpy() for k, v in sk.sinkhorn_forward_select("log", _t(mu), _t(nu), _t(C), lam, 170).items()}
     ref = oracle.forward(mu, nu, C[None], lam, 170)
-    assert loss_rel_err(out["loss"].cpu().numpy(), ref["loss"]) <= 1e-4
+    if case != "spread":  # dropping the entry would show in every result
+        other = oracle.forward(mu, nu, split[None], lam, 170)
+        assert loss_rel_err(other["loss"], ref["loss"]) > 1e-2
+        assert max(gauge_fixed_errors(mu, nu, other["alpha"], other["beta"], ref["alpha"], ref["beta"])) > 1e-1
+    assert loss_rel_err(out["loss"], ref["loss"]) <= 1e-4
+    ea, eb = gauge_fixed_errors(mu, nu, out["alpha"], out["beta"], ref["alpha"], ref["beta"])
+    assert max(ea, eb) <= 1e-3 * max(1.0, 0.03 / lam)
+    for k in out:
+        np.testing.assert_array_equal(out[k], log[k])  # the sweeps
+
+
+@pytest.mark.parametrize("d, at", [(4096, (4095, 4095)), (4096, (4094, 63)), (1600, (1, 1599))])
+def test_every_entry_of_a_large_cost_counts(d, at):
+    """Rows beyond the first pass of the cost's test (1024 work-groups of four)."""
+    h = int(d ** 0.5)
+    mu, nu, C = make(17, 8, (h, h), (h, h), "sq")
+    C[at] += 1e-3
+    out = sk.sinkhorn_forward(_t(mu), _t(nu), _t(C), 0.05, 150)
+    log = sk.sinkhorn_forward_select("log", _t(mu), _t(nu), _t(C), 0.05, 150)
+    assert "sk_sep_solve" in sk.sinkhorn_describe(8, d, d, 0, 0.05, 150)
+    for k in out:
+        assert torch.equal(out[k], log[k]), k
 
 
 def returned_error(g, mu, nu, C, lam, side):
