@@ -478,8 +478,9 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
 // for each): a work-group takes 64 columns, 16 threads of 4 columns by 16 row
 // groups; row group q sums every 16th row block, the groups are added in order.
 // The slices of a problem then are ceil(d2 / 64), and the longest chain of
-// loads R / 16 (sk_tiled_merge_cols: R, in steps of 16).  Measured on 8
-// problems of 784 columns with 392 row blocks: 25 us there.
+// loads R / 16 (sk_tiled_merge_cols: R, in steps of 16).  (One work-group per
+// problem through 392 row blocks of 784 columns took 25 us; such a problem has
+// 98 since a row block holds at least a staged chunk.)
 template <int NT, bool PLAIN>
 __global__ __launch_bounds__(NT) void sk_tiled_merge_rows(TiledArgs T, int k) {
     static_assert(NT == 256, "16 columns groups by 16 row groups");
@@ -1859,7 +1860,8 @@ int shared_width(int B, int d1, int d2, int kind) {
 // Row blocks.  One problem per work-group: enough work-groups for ~2048
 // wavefronts, rows per block a multiple of the wavefronts per group.  Shared
 // cost: ~256 (wide rows) or ~512 work-groups, the count of row blocks a
-// multiple of 8 when the rows allow it so that a row block stays on one XCD.
+// multiple of 8 so that a row block stays on one XCD, unless the rows or the
+// least size of a block (small batches) say otherwise.
 bool stream_shape(int d2, int kind);
 int stream_waves(int d2);
 
