@@ -1939,12 +1939,18 @@ int padded_width(int d2, int kind) {
 }
 
 // The merge splits the row blocks too (sk_tiled_merge_rows) from 32 of them,
-// while a problem has at most 1024 slices of 64 columns: the slices' errors are
-// added in fixed point at 2^(45 - log2 slices) units per unit of error (see
-// take_stop), at 1024 slices within 512 of 2^35 units, 1.5e-8; of 16384 slices
-// (2^20 columns) a sum of up to 4e-6 could read as 0, and 32768 no longer fit
-// the count's 15 bits.  (Slices of 1024 columns are 16384 at most.)
-bool merge_by_rows(int R, int d2) { return R >= 32 && d2 <= 64 * 1024; }
+// while its slices of 64 columns fit a grid dimension.  Under an early stop
+// every slice also adds to its problem's accumulator, one atomic in turn: beyond
+// 800 work-groups that costs more than the shorter chains give, unless a
+// problem's slices are few (40 iterations, by rows and by columns: 8 problems of
+// 4096 columns 2.24 and 2.47 ms, 12 3.19 each, 32 5.86 and 5.53; 128 of 500
+// columns 0.85 and 0.95; without a stop never more).  So a problem has at most
+// 800 slices there, far below what the accumulator's 15-bit count and its fixed
+// point, 2^(45 - log2 slices) units per unit of error, can take.
+bool merge_by_rows(int R, int B, int d2, float tol) {
+    const int slices = (d2 + 63) / 64;
+    return R >= 32 && slices <= 65535 && !(tol > 0.f && slices > 8 && (int64_t)B * slices > 800);
+}
 // Work-groups per problem of the merge after a sweep (4 columns per thread).
 int merge_slices(int d2) { return (d2 + 4 * kMergeColsThreads - 1) / (4 * kMergeColsThreads); }
 
@@ -2248,7 +2254,7 @@ TiledArgs tiled_args(const FwdArgs &a, int kind, void *ws, Layout *Lout) {
     T.sep_mode = nullptr;
     T.sep = nullptr;
     T.plain = PlainArgs{};
-    T.merge_rows = merge_by_rows(R, a.d2);
+    T.merge_rows = merge_by_rows(R, a.B, a.d2, a.tol);
     T.MS = T.merge_rows ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     // A merge in slices has its accumulators in their own region, else in the
     // loss partials' (8 bytes per problem of at least 4 R; they are written
@@ -2450,10 +2456,10 @@ int tiled_describe(const FwdArgs &a, char *buf, size_t len) {
         snprintf(sweep, sizeof sweep, "sk_tiled_sweep<%d> (one problem per work-group)", ncw);
     }
     char mrg[128];
-    const int slices = merge_by_rows(R, a.d2) ? (a.d2 + 63) / 64 : merge_slices(a.d2);
+    const int slices = merge_by_rows(R, B, a.d2, a.tol) ? (a.d2 + 63) / 64 : merge_slices(a.d2);
     if (merge)
         snprintf(mrg, sizeof mrg, "%s<%d> after each sweep (%d work-group%s per problem)",
-                 merge_by_rows(R, a.d2) ? "sk_tiled_merge_rows" : "sk_tiled_merge_cols", kMergeColsThreads, slices,
+                 merge_by_rows(R, B, a.d2, a.tol) ? "sk_tiled_merge_rows" : "sk_tiled_merge_cols", kMergeColsThreads, slices,
                  slices == 1 ? "" : "s");
     else
         snprintf(mrg, sizeof mrg, "the merge folded into the next sweep");

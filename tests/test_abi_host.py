@@ -183,13 +183,18 @@ def test_few_wide_problems_take_the_faster_sweep(B, d1, d2, shared):
     assert ("sk_tiled_sweep_shared<" in line) == shared and "sk_tiled_sweep" in line
 
 
-@pytest.mark.parametrize("d2, merge", [(65536, "rows"), (65537, "cols"), (2097152, "cols"), (1 << 24, "cols")])
-def test_merge_slices_of_the_widest_rows(d2, merge):
-    # The early stop counts a problem's slices in 15 bits, and they are a grid dimension: at most 16384 (the widest
-    # rows, 1024 columns each).
-    line = sk.sinkhorn_describe(1, 128, d2, 0, 0.1, 10, 1e-3)
+@pytest.mark.parametrize("B, d2, tol, merge", [
+    (1, 4194240, 0.0, "rows"), (1, 4194241, 0.0, "cols"), (1, 1 << 24, 0.0, "cols"),
+    (1, 51200, 1e-3, "rows"), (1, 51201, 1e-3, "cols"), (1, 2097152, 1e-3, "cols"), (1, 1 << 24, 1e-3, "cols"),
+    (12, 4096, 1e-3, "rows"), (13, 4096, 1e-3, "cols"), (13, 4096, 0.0, "rows"),
+])
+def test_merge_slices(B, d2, tol, merge):
+    # The slices of a problem are a grid dimension; under an early stop they are counted in 15 bits, and many of them
+    # are slower.
+    line = sk.sinkhorn_describe(B, 4096 if d2 == 4096 else 128, d2, 0, 0.1, 10, tol)
     m = re.search(r"sk_tiled_merge_(\w+)<256> after each sweep \((\d+) work-group", line)
-    assert m and m.group(1) == merge and int(m.group(2)) <= 16384, line
+    assert m and m.group(1) == merge, line
+    assert int(m.group(2)) <= (32767 if tol > 0 else 65535)
 
 
 def test_points_workspace_sizes():

@@ -31,6 +31,7 @@ def _t(x):
     (1, 300, 2100, False, 0.0, "rows"),  # enough rows for the shared-cost sweep
     (3, 301, 2305, False, 1e-3, "rows"),
     (2, 70, 2901, False, 0.0, "cols"),
+    (20, 300, 2700, False, 1e-3, "cols"),  # 75 row blocks, but 860 slices under an early stop
     (1, 64, 200, False, 0.0, "cols"),    # 16 row blocks: the exact merge of one wavefront
     (1, 68, 200, False, 0.0, "cols"),    # 17: of 16
 ])
