@@ -395,7 +395,7 @@ def main():
         sweeps = (tfwd[n_hi][1] - tfwd[n_lo][1]) / prob.B  # sweeps per problem between the two runs
         kernel_ms = (tfwd[n_hi][0] - tfwd[n_lo][0]) / max(sweeps, 1.0)
         cells = float(prob.B) * prob.d1 * prob.d2
-        src = kernel_source_hash(["sk_tiled.hip", "sk_device.h"])
+        src = kernel_source_hash(["sk_tiled.hip", "sk_tiled_plain.h", "sk_device.h"])
         if points:
             # The cost is recreated from the coordinates: nothing streams, the
             # sweep is bound by one exp2 per cell (plus the distance arithmetic);
@@ -418,14 +418,18 @@ def main():
             # grid splits over the axes, so an iteration is four sets of line
             # sums (2 side d cells each way, one fused multiply-add per cell)
             # in one kernel, plus the sweep's and the merge's launches that
-            # find every problem solved.
+            # find every problem solved.  (The metric's cell updates stay
+            # B d1 d2 per iteration, cells that this form does not compute one
+            # by one.)  The stored counters are of whole solves, one launch for
+            # all iterations.
             kname = "sk_sep_solve"
             src = kernel_source_hash(["sk_separable.hip", "sk_device.h"])
             side = round(prob.d1 ** 0.5)
             achieved = 2.0 * 4.0 * side * prob.d1 * prob.B / (kernel_ms * 1e-3) / 1e12
             roof = dict(bound="alu", achieved=round(achieved, 4), peak=PEAK_FP32_VALU, unit="TFLOP/s",
                         frac=round(achieved / PEAK_FP32_VALU, 4), kernel=kname + " + two launches with nothing to do",
-                        kernel_ms=round(kernel_ms, 5), work="fp32 flops per iteration = 8*B*side*d1 (line sums)")
+                        kernel_ms=round(kernel_ms, 5), work="fp32 flops per iteration = 8*B*side*d1 (line sums)",
+                        traffic_of="one launch of sk_sep_solve, all iterations")
         else:
             # A shared cost's iteration is the sweep plus the merge of its
             # row-block partials (a short launch that also takes the stop
