@@ -426,7 +426,7 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_cols(TiledArgs T, int k) {
     }
     const int st = T.state[b];
     if (st != 0) {  // block-uniform
-        if (PLAIN && st == kPlainState) plain_v<NT / 64>(T, lds, sl * T.B + b, T.MS * T.B);
+        if (PLAIN && st == kPlainState) plain_v<NT / 64, false>(T, lds, sl * T.B + b, T.MS * T.B);
         return;
     }
     const size_t rstride = (size_t)T.B * T.d2p / 4;  // one row block, in f4v
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(NT) void sk_tiled_merge_rows(TiledArgs T, int k) {
     }
     const int st = T.state[b];
     if (st != 0) {  // block-uniform
-        if (PLAIN && st == kPlainState) plain_v<NT / 64>(T, lds, sl * T.B + b, T.MS * T.B);
+        if (PLAIN && st == kPlainState) plain_v<NT / 64, false>(T, lds, sl * T.B + b, T.MS * T.B);
         return;
     }
     const size_t rstride = (size_t)T.B * T.d2p / 4;  // one row block, in f4v
@@ -1222,7 +1222,7 @@ __global__ __launch_bounds__(64 * W, PLAIN ? shared_occupancy(NCW, W) : 1) void 
     const bool skip = b_raw >= T.B || (!STATS && st != 0);
     if (!__syncthreads_or(!skip)) {
         if (PLAIN && plain_taken(T))
-            plain_u<W>(T, lds, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
+            plain_u<W, false>(T, lds, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
         return;
     }
 
@@ -2012,12 +2012,16 @@ void launch_merge_exact(const TiledArgs &T, hipStream_t st) {
 // work-group of a compacted batch.
 void launch_merge(const TiledArgs &T, int k, hipStream_t st) {
     const dim3 grid(T.B + (T.order ? 1 : 0), T.MS);
-    const size_t lds = T.plain.range ? sizeof(float) * 1024 * (kMergeColsThreads / 64) : 0;
+    // The last merge beside the plain form runs no product: sk_plain_last does.
+    const bool plain = T.plain.range && k + 1 < T.n_iter;
+    const size_t lds = plain ? sizeof(float) * 1024 * (kMergeColsThreads / 64) : 0;
     auto go = [&](auto *kernel) { hipLaunchKernelGGL(*kernel, grid, dim3(kMergeColsThreads), lds, st, T, k); };
     if (T.merge_rows)
-        T.plain.range ? go(&sk_tiled_merge_rows<kMergeColsThreads, true>) : go(&sk_tiled_merge_rows<kMergeColsThreads, false>);
+        plain ? go(&sk_tiled_merge_rows<kMergeColsThreads, true>) : go(&sk_tiled_merge_rows<kMergeColsThreads, false>);
     else
-        T.plain.range ? go(&sk_tiled_merge_cols<kMergeColsThreads, true>) : go(&sk_tiled_merge_cols<kMergeColsThreads, false>);
+        plain ? go(&sk_tiled_merge_cols<kMergeColsThreads, true>) : go(&sk_tiled_merge_cols<kMergeColsThreads, false>);
+    if (T.plain.range && !plain)
+        hipLaunchKernelGGL((sk_plain_last<4, false>), dim3(512), dim3(256), sizeof(float) * 1024 * 4, st, T);
 }
 void launch_final(const TiledArgs &T, hipStream_t st) {
     if (T.d2 > 1024)
@@ -2064,8 +2068,13 @@ hipError_t run_sequence(const TiledArgs &T, hipStream_t st, Sweep sweep, Stats s
         }
         launch_col_exact(T, st);
         launch_merge_exact(T, st);
-        if (T.plain.range)
-            hipLaunchKernelGGL(sk_plain_first, dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
+        if (T.plain.range) {
+            constexpr size_t lds = sizeof(float) * 1024 * 8;
+            if (T.n_iter == 1)
+                hipLaunchKernelGGL(sk_plain_first<true>, dim3(512), dim3(512), lds, st, T);
+            else
+                hipLaunchKernelGGL(sk_plain_first<false>, dim3(512), dim3(512), lds, st, T);
+        }
         for (int k = 1; k <= T.n_iter; ++k) {
             sweep(k);
             if (k < T.n_iter) launch_merge(T, k, st);
@@ -2148,7 +2157,6 @@ hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
         [&]() {
             if (T.plain.range) {
                 hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
-                hipLaunchKernelGGL((sk_plain_last<4, false>), dim3(512), dim3(256), sizeof(float) * 1024 * 4, st, T);
                 hipLaunchKernelGGL(*finish, dim3(T.B), dim3(64 * kRedoWaves<NCW>), finish_lds, st, T);
             }
             hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0);

@@ -167,13 +167,13 @@ __device__ __forceinline__ bool plain_taken(const TiledArgs &T) { return T.plain
 // out[m][n] = mass[m][n] / sum_k A[k][m] X[k][n] over m < M, n < N in tiles of
 // 32 x 32: work-groups wg, wg + nwg, ... of NW wavefronts; lds: NW * 1024
 // floats.  kd is a multiple of 32; out's rows and columns past its size keep
-// 0.  SUMS: out takes the sums themselves.  One batch of
+// 0.  SUMS: the sums take the masses' place, for the potentials.  One batch of
 // loads is in flight beside a batch's products: bound by those loads (20 cycles
 // per 256 bytes and CU), so loading further ahead only adds batches that are
 // thrown away (15.2 us with three more, 12.7 so).
 constexpr int kPlainUnroll = 8;  // matrix instructions (2 of the contraction each) per batch of loads
 template <int NW, bool SUMS>
-__device__ __forceinline__ void plain_product(const float *A, int lda, const float *X, const float *mass, float *out,
+__device__ __forceinline__ void plain_product(const float *A, int lda, const float *X, float *mass, float *out,
                                               int ldx, int kd, int M, int N, int32_t *bad, float *lds, int wg,
                                               int nwg) {
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -222,49 +222,47 @@ __device__ __forceinline__ void plain_product(const float *A, int lda, const flo
             if (m < M && n < N) {
                 const size_t at = (size_t)m * ldx + n;
                 const float mm = mass[at];
-                float v = SUMS ? s : 0.f;
+                float v = 0.f;
                 if (mm > 0.f) {
                     if (!(s >= kPlainLo && s <= kPlainHi)) bad[n] = 1;
-                    if (!SUMS) v = mm * __builtin_amdgcn_rcpf(s);
+                    v = mm * __builtin_amdgcn_rcpf(s);
                 }
                 out[at] = v;
+                if (SUMS) mass[at] = s;
             }
         }
         __syncthreads();
     }
 }
-template <int NW>
+template <int NW, bool SUMS>
 __device__ __forceinline__ void plain_u(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW, false>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, plain_bad(P, T.B), lds, wg, nwg);
+    plain_product<NW, SUMS>(P.Kt, P.l1, P.Vt, P.mut, P.Ut, P.lb, P.p2, T.d1, T.B, plain_bad(P, T.B), lds, wg, nwg);
 }
-template <int NW>
+template <int NW, bool SUMS>
 __device__ __forceinline__ void plain_v(const TiledArgs &T, float *lds, int wg, int nwg) {
     const PlainArgs &P = T.plain;
-    plain_product<NW, false>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, plain_bad(P, T.B), lds, wg, nwg);
+    plain_product<NW, SUMS>(P.K, P.l2, P.Ut, P.nut, P.Vt, P.lb, P.p1, T.d2, T.B, plain_bad(P, T.B), lds, wg, nwg);
 }
 // The first v-update.
+template <bool SUMS>
 __global__ __launch_bounds__(512) void sk_plain_first(TiledArgs T) {
     extern __shared__ float lds[];
     if (!plain_taken(T)) return;
-    plain_v<8>(T, lds, (int)blockIdx.x, (int)gridDim.x);
+    plain_v<8, SUMS>(T, lds, (int)blockIdx.x, (int)gridDim.x);
 }
-// The sums of the last u-update (8 wavefronts, as the sweeps) or v-update (4, as
-// the merges) again, in the masses' place: the last sweep runs no product, so
-// Ut still is what the last v-update took.  (Kept out of the two launches of an
-// iteration: a test for the last one there moved the sweep's code, 1.2 % on a
-// cost out of range.)
+// The last u-update (8 wavefronts, as beside the sweeps) or v-update (4, as
+// beside the merges), keeping the sums.  Launches of their own: a test for the
+// last one in the iteration's launches moved the sweep's code, 1.2 % on a cost
+// out of range.
 template <int NW, bool ROWS>
 __global__ __launch_bounds__(64 * NW) void sk_plain_last(TiledArgs T) {
     extern __shared__ float lds[];
     if (!plain_taken(T)) return;
-    const PlainArgs &P = T.plain;
-    int32_t *bad = plain_bad(P, T.B);
-    const int wg = (int)blockIdx.x, nwg = (int)gridDim.x;
     if (ROWS)
-        plain_product<NW, true>(P.Kt, P.l1, P.Vt, P.mut, P.mut, P.lb, P.p2, T.d1, T.B, bad, lds, wg, nwg);
+        plain_u<NW, true>(T, lds, (int)blockIdx.x, (int)gridDim.x);
     else
-        plain_product<NW, true>(P.K, P.l2, P.Ut, P.nut, P.nut, P.lb, P.p1, T.d2, T.B, bad, lds, wg, nwg);
+        plain_v<NW, true>(T, lds, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // log2(mass / sum), -inf without mass, to half a unit in the last place: the

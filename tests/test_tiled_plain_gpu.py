@@ -48,6 +48,17 @@ def test_plain_tiled(B, d1, d2, lam, zero):
     assert el <= LOSS and ep <= POT
 
 
+@pytest.mark.parametrize("B, n_iter", [(38000, 1), (19000, 2)])
+def test_plain_tiled_few_iterations(B, n_iter):
+    """The last products are the first ones."""
+    rng = np.random.default_rng(50)
+    C = rng.random((640, 640), dtype=np.float32)
+    mu, nu = (0.05 + rng.random((64, 640)) for _ in range(2))
+    mu, nu = (np.tile((h / h.sum(1, keepdims=True)).astype(np.float32), (B // 64 + 1, 1))[:B] for h in (mu, nu))
+    _, _, el, ep = run(mu, nu, C, 0.05, n_iter, [0, 63, 64, B - 1])
+    assert el <= LOSS and ep <= POT
+
+
 def test_cost_out_of_range():
     p = workloads.random_problem(42, 224, 640, 640, 0.0222, 120)  # 65 bits
     _, _, el, ep = run(p.mu, p.nu, p.C, p.lam, 120, [0, 223])
