@@ -2137,30 +2137,29 @@ hipError_t run_shared(const TiledArgs &T, hipStream_t st) {
     auto stats_kernel = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, true, false>;
     hipError_t e = allow_lds(stats_kernel, lds);
     if (e != hipSuccess) return e;
-    // The last sweep beside the plain form runs no product (see sk_plain_last).
-    constexpr size_t finish_lds = sizeof(float) * kRedoWaves<NCW> * NCW * 64;
-    auto finish = &sk_plain_finish<NCW>;
     auto sweep = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, false>;
-    auto both = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>;
     e = allow_lds(sweep, lds);
-    if (e == hipSuccess && T.plain.range) e = allow_lds(both, lds);
-    if (e == hipSuccess && T.plain.range) e = allow_lds(finish, finish_lds);
     if (e != hipSuccess) return e;
-    return run_sequence(
-        T, st,
-        [&](int k) {
-            if (T.plain.range && k < T.n_iter)
-                hipLaunchKernelGGL(*both, grid, blk, lds, st, T, k);
-            else
-                hipLaunchKernelGGL(*sweep, grid, blk, lds, st, T, k);
-        },
-        [&]() {
-            if (T.plain.range) {
-                hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
-                hipLaunchKernelGGL(*finish, dim3(T.B), dim3(64 * kRedoWaves<NCW>), finish_lds, st, T);
-            }
-            hipLaunchKernelGGL(*stats_kernel, grid, blk, lds, st, T, 0);
-        });
+    auto launch = [&](auto *kernel, int k) { hipLaunchKernelGGL(*kernel, grid, blk, lds, st, T, k); };
+    if constexpr (NCW > 4) {  // (plain_wanted asks for more than 256 columns)
+        if (T.plain.range) {
+            constexpr size_t finish_lds = sizeof(float) * kRedoWaves<NCW> * NCW * 64;
+            auto finish = &sk_plain_finish<NCW>;
+            auto both = &sk_tiled_sweep_shared<NCW, W, RS, RB, VEC4, false, true>;
+            e = allow_lds(both, lds);
+            if (e == hipSuccess) e = allow_lds(finish, finish_lds);
+            if (e != hipSuccess) return e;
+            // The last sweep beside the plain form runs no product: sk_plain_last does.
+            return run_sequence(
+                T, st, [&](int k) { k < T.n_iter ? launch(both, k) : launch(sweep, k); },
+                [&]() {
+                    hipLaunchKernelGGL((sk_plain_last<8, true>), dim3(512), dim3(512), sizeof(float) * 1024 * 8, st, T);
+                    hipLaunchKernelGGL(*finish, dim3(T.B), dim3(64 * kRedoWaves<NCW>), finish_lds, st, T);
+                    launch(stats_kernel, 0);
+                });
+        }
+    }
+    return run_sequence(T, st, [&](int k) { launch(sweep, k); }, [&]() { launch(stats_kernel, 0); });
 }
 
 template <int NCW, int D>
