@@ -35,7 +35,7 @@
 // all padded with zeros to multiples of 32, so every operand load is two runs
 // of 128 bytes and nothing is masked; rows lie an odd number of 256-byte lines
 // apart, so that a column's rows spread over the L2's channels.  Measured on
-// 256 problems of 1000 x 1000: 12.9 and 13.6 us for the two launches (sweep
+// 256 problems of 1000 x 1000: 12.5 and 13.4 us for the two launches (sweep
 // and merge: 64.6 and 5.8), 4.3 of each the launch, the setup and the merge;
 // the matrix cores alone would take 3.3, the loads of the operands set the pace.
 #pragma once
